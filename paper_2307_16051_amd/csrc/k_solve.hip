@@ -572,99 +572,162 @@ hipError_t launch_trsv_upper_f64(int64_t n, const double *LU, int64_t lda, const
 }
 
 // ---------------------------------------------------------------- matvec
-// Partial sums of A u over column chunks (FP64 accumulation of FP32 data),
-// then a fixed-order reduction: r = b - sum (b may be null: r = sum).
-constexpr int MV_ROWS = 256, MV_CH = 256;
-
-__global__ __launch_bounds__(256) void k_gemv_f32_part(int64_t n, const float *__restrict__ A,
-                                                       int64_t lda, const float *__restrict__ u,
-                                                       double *__restrict__ part)
+// r = b - A u (b may be null: r = sum), FP64 accumulation of FP32 data, two
+// forms by size (launch_gemv_resid).
+//
+// One launch, n <= MV_ONE_N: a workgroup of 1024 threads owns MV_RB = 32 rows
+// over all columns; a wavefront reads two columns' 128-byte pieces per load,
+// each lane takes every 32nd column, eight loads in flight, and the 32
+// column groups of a row are summed through LDS in a fixed order.  At these
+// sizes the matrix comes from the caches and what bounds the product is how
+// many loads are in flight: with one row (or four) per thread and 256
+// columns in series the grid had ceil(n/1024) x ceil(n/256) workgroups of
+// four wavefronts.  Measured, this form against that one (the reduction's
+// launch included): n = 256 3.4 against 32 us, 1000 4.5 / 33, 2048 6.1 / 35,
+// 4096 14.7 / 73 (4.6 TB/s).
+// lane's part: rows [i0, i0 + MV_RB) of A (lda), us = u in LDS; the sum of
+// row i0 + t is returned to threads t < MV_RB (0 to the others).
+constexpr int MV_RB = 32, MV_NT = 1024, MV_UN = 8;
+__device__ __forceinline__ double gemv_rows(int64_t n, const float *__restrict__ A, int64_t lda,
+                                            const float *__restrict__ us, int64_t i0,
+                                            double (*__restrict__ sh)[MV_RB])
 {
-    __shared__ float ush[MV_CH];
-    const int64_t j0 = (int64_t)blockIdx.y * MV_CH;
-    const int64_t jn = std::min<int64_t>(MV_CH, n - j0);
-    if (threadIdx.x < jn) ush[threadIdx.x] = u[j0 + threadIdx.x];
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * MV_ROWS + threadIdx.x;
-    if (i >= n) return;
-    const float *ap = A + i + j0 * lda;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int64_t c = 0;
-    for (; c + 4 <= jn; c += 4) {
-        s0 += (double)ap[(c + 0) * lda] * (double)ush[c + 0];
-        s1 += (double)ap[(c + 1) * lda] * (double)ush[c + 1];
-        s2 += (double)ap[(c + 2) * lda] * (double)ush[c + 2];
-        s3 += (double)ap[(c + 3) * lda] * (double)ush[c + 3];
-    }
-    for (; c < jn; ++c) s0 += (double)ap[c * lda] * (double)ush[c];
-    part[(int64_t)blockIdx.y * n + i] = (s0 + s1) + (s2 + s3);
-}
-
-// The same partial sums with four consecutive rows per thread (one 16-byte
-// load per column, so a wavefront reads 1 KB contiguous): needs n, lda and A
-// 16-byte aligned.  Per row the same four sums in the same order as above,
-// so the results are identical.
-constexpr int MV_ROWS4 = 1024;
-__global__ __launch_bounds__(256) void k_gemv_f32_part4(int64_t n, const float *__restrict__ A,
-                                                        int64_t lda, const float *__restrict__ u,
-                                                        double *__restrict__ part)
-{
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    __shared__ float ush[MV_CH];
-    const int64_t j0 = (int64_t)blockIdx.y * MV_CH;
-    const int64_t jn = std::min<int64_t>(MV_CH, n - j0);
-    if (threadIdx.x < jn) ush[threadIdx.x] = u[j0 + threadIdx.x];
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * MV_ROWS4 + 4 * (int64_t)threadIdx.x;
-    if (i >= n) return;
-    const float *ap = A + i + j0 * lda;
-    double s[4][4];
+    constexpr int G = MV_NT / MV_RB;
+    const int t = threadIdx.x;
+    const int64_t i = i0 + t % MV_RB;
+    const float *ap = A + (i < n ? i : n - 1);  // rows past the end read row n - 1
+    double s0 = 0.0, s1 = 0.0;
+    int64_t j = t / MV_RB;
+    for (; j + (int64_t)(MV_UN - 1) * G < n; j += (int64_t)MV_UN * G) {
+        float a[MV_UN];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+        for (int k = 0; k < MV_UN; ++k) a[k] = ap[(j + (int64_t)k * G) * lda];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) s[q][k] = 0.0;
-    int64_t c = 0;
-    for (; c + 4 <= jn; c += 4) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const f4 a = *(const f4 *)(ap + (c + k) * lda);
-            const double uk = (double)ush[c + k];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s[q][k] += (double)a[q] * uk;
+        for (int k = 0; k < MV_UN; k += 2) {
+            s0 += (double)a[k] * (double)us[j + k * G];
+            s1 += (double)a[k + 1] * (double)us[j + (k + 1) * G];
         }
     }
-    for (; c < jn; ++c) {
-        const f4 a = *(const f4 *)(ap + c * lda);
-        const double uk = (double)ush[c];
+    float a[MV_UN];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s[q][0] += (double)a[q] * uk;
+    for (int k = 0; k < MV_UN; ++k) {  // the last columns: index clamped, then left out
+        const int64_t jj = j + (int64_t)k * G;
+        a[k] = ap[(jj < n ? jj : n - 1) * lda];
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        part[(int64_t)blockIdx.y * n + i + q] = (s[q][0] + s[q][1]) + (s[q][2] + s[q][3]);
+    for (int k = 0; k < MV_UN; ++k) {
+        const int64_t jj = j + (int64_t)k * G;
+        if (jj < n) s0 += (double)a[k] * (double)us[jj];
+    }
+    double s = s0 + s1;
+    s += __shfl_xor(s, MV_RB);
+    if ((t & 63) < MV_RB) sh[t >> 6][t & 63] = s;
+    __syncthreads();
+    double q = 0.0;
+    if (t < MV_RB) {
+#pragma unroll
+        for (int w = 0; w < MV_NT / 64; ++w) q += sh[w][t];
+    }
+    return q;
 }
 
-__global__ void k_gemv_finish(int64_t n, int nch, const double *__restrict__ part,
-                              const float *__restrict__ b, float *__restrict__ r)
+constexpr int64_t MV_ONE_N = 4096;
+__global__ __launch_bounds__(MV_NT) void k_gemv_rows(int64_t n, const float *__restrict__ A,
+                                                     int64_t lda, const float *__restrict__ u,
+                                                     const float *__restrict__ b,
+                                                     float *__restrict__ r)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    __shared__ float us[MV_ONE_N];
+    __shared__ double sh[MV_NT / 64][MV_RB];
+    for (int64_t j = threadIdx.x; j < n; j += MV_NT) us[j] = u[j];
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * MV_RB + threadIdx.x;
+    const double q = gemv_rows(n, A, lda, us, (int64_t)blockIdx.x * MV_RB, sh);
+    if (threadIdx.x < MV_RB && i < n) r[i] = b ? (float)((double)b[i] - q) : (float)q;
+}
+
+// Larger n: partial sums over chunks of MV_CH columns, then their sum in a
+// fixed order.  A workgroup of eight wavefronts owns 64 rows of one chunk,
+// one row per lane, 32 columns per wavefront with 16 loads in flight (any
+// alignment).  HBM-bound: n = 8192 44 us (6.2 TB/s, the sum included; 88 us
+// with one or four rows per thread and the chunk's columns in series),
+// 5003 26 / 32, 12000 101 / 169, 16384 188 / 206.
+constexpr int MV_CH = 256, MV_CW = 8;
+__global__ __launch_bounds__(MV_CW * 64) void k_gemv_part(int64_t n, const float *__restrict__ A,
+                                                          int64_t lda, const float *__restrict__ u,
+                                                          double *__restrict__ part)
+{
+    constexpr int PW = MV_CH / MV_CW, UN = 16;  // columns per wavefront, in flight
+    __shared__ float ush[MV_CH];
+    __shared__ double sh[MV_CW][64];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t j0 = (int64_t)blockIdx.y * MV_CH;
+    const int jn = (int)std::min<int64_t>(MV_CH, n - j0);
+    if (t < MV_CH) ush[t] = t < jn ? u[j0 + t] : 0.0f;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    const float *ap = A + (i < n ? i : n - 1) + j0 * lda;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 1
+    for (int c = w * PW; c < (w + 1) * PW; c += UN) {
+        float a[UN];
+#pragma unroll
+        for (int k = 0; k < UN; ++k) a[k] = ap[(int64_t)std::min(c + k, jn - 1) * lda];
+#pragma unroll
+        for (int k = 0; k < UN; k += 2) {  // columns past the end: clamped and left out
+            if (c + k < jn) s0 += (double)a[k] * (double)ush[c + k];
+            if (c + k + 1 < jn) s1 += (double)a[k + 1] * (double)ush[c + k + 1];
+        }
+    }
+    sh[w][lane] = s0 + s1;
+    __syncthreads();
+    if (t < 64 && i < n) {
+        double q = 0.0;
+#pragma unroll
+        for (int k = 0; k < MV_CW; ++k) q += sh[k][t];
+        part[(int64_t)blockIdx.y * n + i] = q;
+    }
+}
+
+// the chunks of 32 rows per workgroup, eight chunks at a time (with one row
+// per thread the chain over the chunks took 20 us at n = 16384; 6 us)
+__global__ __launch_bounds__(256) void k_gemv_finish(int64_t n, int nch, const double *__restrict__ part,
+                                                     const float *__restrict__ b, float *__restrict__ r)
+{
+    __shared__ double sh[8][32];
+    const int t = threadIdx.x, g = t >> 5;
+    const int64_t i = (int64_t)blockIdx.x * 32 + (t & 31);
+    const int64_t ic = std::min<int64_t>(i, n - 1);
     double s = 0.0;
-    for (int c = 0; c < nch; ++c) s += part[(int64_t)c * n + i];
-    r[i] = b ? (float)((double)b[i] - s) : (float)s;
+#pragma unroll 8
+    for (int c = g; c < nch; c += 8) s += part[(int64_t)c * n + ic];
+    sh[g][t & 31] = s;
+    __syncthreads();
+    if (t < 32 && i < n) {
+        double q = 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) q += sh[k][t];
+        r[i] = b ? (float)((double)b[i] - q) : (float)q;
+    }
 }
 
 hipError_t launch_gemv_resid(int64_t n, const float *A, int64_t lda, const float *u, const float *b,
                              float *r, double *part, hipStream_t s)
 {
+    // one launch up to MV_ONE_N: there both forms take the same time (14.7
+    // and 14.0 us at 4096), and below it the second launch costs more than it
+    // saves.  It writes rows of r while other workgroups still read u and A,
+    // so a caller's r that overlaps either takes the two launches.
+    const auto apart = [&](const float *p, int64_t len) { return r + n <= p || p + len <= r; };
+    if (n <= MV_ONE_N && apart(u, n) && apart(A, (n - 1) * lda + n)) {
+        hipLaunchKernelGGL(k_gemv_rows, dim3((unsigned)((n + MV_RB - 1) / MV_RB)), dim3(MV_NT), 0,
+                           s, n, A, lda, u, b, r);
+        return hipGetLastError();
+    }
     const int nch = (int)((n + MV_CH - 1) / MV_CH);
-    if (n % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0)
-        hipLaunchKernelGGL(k_gemv_f32_part4, dim3((unsigned)((n + MV_ROWS4 - 1) / MV_ROWS4), nch),
-                           dim3(256), 0, s, n, A, lda, u, part);
-    else
-        hipLaunchKernelGGL(k_gemv_f32_part, dim3((unsigned)((n + MV_ROWS - 1) / MV_ROWS), nch),
-                           dim3(256), 0, s, n, A, lda, u, part);
-    hipLaunchKernelGGL(k_gemv_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, nch,
+    hipLaunchKernelGGL(k_gemv_part, dim3((unsigned)((n + 63) / 64), nch), dim3(MV_CW * 64), 0, s, n,
+                       A, lda, u, part);
+    hipLaunchKernelGGL(k_gemv_finish, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, s, n, nch,
                        (const double *)part, b, r);
     return hipGetLastError();
 }
@@ -899,39 +962,29 @@ __global__ __launch_bounds__(B_SOLVE_THREADS) void k_b_solve(const BDesc *__rest
     }
 }
 
-// r = b - J u with FP64 accumulation; items are 256-row blocks of a slot
-__global__ __launch_bounds__(256) void k_b_gemv(const BDesc *__restrict__ d,
-                                                const BState *__restrict__ st, int nslots)
+// r = b - J u with FP64 accumulation; items are MV_RB-row blocks of a slot
+// (gemv_rows: a row's sum does not depend on the workgroup that takes it).
+// With 256-row items, one row per thread, a request of 2048 rows had eight
+// workgroups and 2048 columns in series: 112 us a call for 32 mixed requests.
+__global__ __launch_bounds__(MV_NT) void k_b_gemv(const BDesc *__restrict__ d,
+                                                  const BState *__restrict__ st, int nslots)
 {
     __shared__ float us[B_MAX_NP];
     __shared__ int off[B_MAX_SLOTS + 1];
+    __shared__ double sh[MV_NT / 64][MV_RB];
     const int total = b_offsets(nslots, off, [&](int s) {
-        return (st[s].phase == BP_RUN && st[s].factor && st[s].ir_on) ? (int)((d[s].Np + 255) / 256) : 0;
+        return (st[s].phase == BP_RUN && st[s].factor && st[s].ir_on) ? (int)(d[s].Np / MV_RB) : 0;
     });
     const int t = threadIdx.x;
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
         const int s = b_find(off, nslots, item);
         const BDesc &q = d[s];
         const int64_t n = q.n;
-        for (int64_t j = t; j < n; j += 256) us[j] = q.u[j];
+        for (int64_t j = t; j < n; j += MV_NT) us[j] = q.u[j];
         __syncthreads();
-        const int64_t i = (int64_t)(item - off[s]) * 256 + t;
-        if (i < n) {
-            const float *__restrict__ row = q.J + i;
-            double acc = (double)q.b[i];
-            int64_t j = 0;
-            for (; j + 8 <= n; j += 8) {
-                float a[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = row[(j + u) * n];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) acc -= (double)a[u] * (double)us[j + u];
-            }
-            for (; j < n; ++j) acc -= (double)row[j * n] * (double)us[j];
-            q.r[i] = (float)acc;
-        } else if (i < q.Np) {
-            q.r[i] = 0.0f;
-        }
+        const int64_t i0 = (int64_t)(item - off[s]) * MV_RB, i = i0 + t;
+        const double sum = gemv_rows(n, q.J, n, us, i0, sh);
+        if (t < MV_RB) q.r[i] = i < n ? (float)((double)q.b[i] - sum) : 0.0f;
         __syncthreads();
     }
 }
@@ -948,7 +1001,7 @@ hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots
 
 hipError_t launch_b_gemv(const BDesc *d, const BState *st, int nslots, int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_b_gemv, dim3(grid), dim3(256), 0, s, d, st, nslots);
+    hipLaunchKernelGGL(k_b_gemv, dim3(grid), dim3(MV_NT), 0, s, d, st, nslots);
     return hipGetLastError();
 }
 

@@ -416,6 +416,30 @@ def test_gemv_resid_matches_fp64_definition(env, n):
     assert np.all(np.abs(r - r_ref) <= U32 * np.abs(r_ref) + 1e-14 * scale)
 
 
+@pytest.mark.parametrize("n", [31, 32, 33, 256, 257, 4095, 4096, 4097, 4161])
+@pytest.mark.parametrize("alias", [False, True])
+def test_gemv_resid_row_and_chunk_edges(env, n, alias):
+    """Both forms of r = b - A u (one launch up to 4096 rows, column chunks
+    beyond) at the edges of their tiles, and with r written over u, which
+    takes the two-launch form at every size.  A is a rank-one FP32 matrix
+    with a random diagonal, so the FP64 definition needs no n x n product."""
+    n3p, torch = env
+    rng = np.random.default_rng(n + 7)
+    p, q, d, u, b = (rng.standard_normal(n).astype(np.float32) for _ in range(5))
+    A = torch.from_numpy(q).cuda()[:, None] * torch.from_numpy(p).cuda()[None, :]  # A^T: rows = columns
+    A.diagonal().add_(torch.from_numpy(d).cuda())
+    Ac = A.double().cpu().numpy().T  # the FP32 entries as stored
+    r_ref = b.astype(np.float64) - Ac @ u.astype(np.float64)
+    ut = torch.from_numpy(u).cuda()
+    if alias:
+        r = n3p.gemv_resid_noalloc(A.t(), ut, torch.from_numpy(b).cuda(), r=ut)
+    else:
+        r = n3p.gemv_resid(A.t(), ut, torch.from_numpy(b).cuda())
+    r = r.cpu().numpy().astype(np.float64)
+    scale = np.abs(b) + np.abs(Ac) @ np.abs(u.astype(np.float64))
+    assert np.all(np.abs(r - r_ref) <= U32 * np.abs(r_ref) + 1e-14 * scale)
+
+
 def half_factors(J32):
     """Oracle factorisation of the FP16-rounded matrix, factors rounded to FP16."""
     Jh = J32.astype(np.float16).astype(np.float64)
