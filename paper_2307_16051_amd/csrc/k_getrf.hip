@@ -409,27 +409,6 @@ __global__ __launch_bounds__(WGM *WGN * 64) void k_gemm16_pair(GemmProb p1, Gemm
 }
 
 // ========================================== Schur GEMM, FP32/FP64 matrix cores
-template <typename T> struct mfma16x4;
-// Output layout of the 16x16 fragment: lane l holds column l & 15; register q
-// holds row 4 (l >> 4) + q for the FP32 instruction and row (l >> 4) + 4 q for
-// the FP64 one (checked on gfx950 with an in-bounds probe).
-template <> struct mfma16x4<float> {
-    typedef f32x4 acc_t;
-    static __device__ __forceinline__ int row(int lane, int q) { return 4 * (lane >> 4) + q; }
-    static __device__ __forceinline__ acc_t op(float a, float b, acc_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct mfma16x4<double> {
-    typedef f64x4 acc_t;
-    static __device__ __forceinline__ int row(int lane, int q) { return (lane >> 4) + 4 * q; }
-    static __device__ __forceinline__ acc_t op(double a, double b, acc_t c)
-    {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-};
-
 // 64x64 block tile, 4 waves of 32x32 (2x2 fragments of 16x16), KC = 16.
 template <typename T>
 __global__ __launch_bounds__(256) void k_gemm_mfma4(int M, int N, int K, const T *__restrict__ At,

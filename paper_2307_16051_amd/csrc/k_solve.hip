@@ -93,6 +93,16 @@ template <> struct tagged<double> {
 // sync layout: int ticket at [0]; tagged words (uint64) from byte offset 16
 __device__ __forceinline__ uint64_t *tag_words(int *sync) { return (uint64_t *)(sync + 4); }
 
+// The next block of this launch in dependency order, 0 .. nblocks - 1.  The
+// counter is never reset: the caller clears it once, launches with epochs
+// 1, 2, ... and the same number of blocks each time, so this launch's tickets
+// start at (epoch - 1) nblocks (a launch of its own to clear it took 3 us).
+__device__ __forceinline__ int take_ticket(int *sync, uint32_t epoch, uint32_t nblocks)
+{
+    const uint32_t t = (uint32_t)__hip_atomic_fetch_add(&sync[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (int)(t - (epoch - 1) * nblocks);
+}
+
 // One published value per lane: lane c of a wavefront fetches the word(s) of
 // column c of a tile, re-polls until every lane's tag matches, and then the
 // values are broadcast lane by lane (v_readlane) into the row updates.
@@ -200,62 +210,124 @@ __device__ __forceinline__ void load_tile_row(V (&fv)[BS], const T *__restrict__
 }
 
 // Diagonal-block helpers.  Each block inverts its own BS x BS diagonal block
-// D (held row-major, stride BS, in Dr) and forms Mx = D^{-1} E, with E the
-// neighbouring off-diagonal tile it depends on last (stride BS, in Eb).  Then
-// only one product with the neighbour's solution is left after it arrives:
+// D (row-major in Dr) and forms Mx = D^{-1} E, with E the neighbouring
+// off-diagonal tile it depends on last (in Eb).  Then only one product with
+// the neighbour's solution is left after it arrives:
 // lower x_b = D^{-1} (b_b - sum_{j<b-1} L_bj x_j) - D^{-1} L_{b,b-1} x_{b-1},
 // upper x_b = D^{-1} (y_b - sum_{j>b+1} U_bj x_j) - D^{-1} U_{b,b+1} x_{b+1}.
 // (Rounding differs from substitution only in the order of the sums.)
 //
-// Inverse of the diagonal block, wavefront 0, lane c = column c of the
-// inverse (LOWER: unit lower; else upper with reciprocals rd of its
-// diagonal).  Dr entries on or beyond the diagonal's wrong side are ignored.
-template <typename V, int BS, bool LOWER>
-__device__ __forceinline__ void diag_inverse(const V *__restrict__ Dr, const V *__restrict__ rd,
-                                             V *__restrict__ Di, int lane)
+// This prologue is what a solve of few blocks waits for: the first block
+// cannot publish before it, and at n = 256 it was 15 of 24 us (the tiles
+// fetched one load at a time, and 64 rows substituted by one wavefront).  So
+// all 32 loads of a thread go out together, and the inverse is built by
+// blocks on all four wavefronts: four 16 x 16 inverses by substitution, then
+// 16 -> 32 -> 64 by X = -D_aa^{-1} (D_ab D_bb^{-1}) on the FP32 / FP64 matrix
+// cores, which also form Mx: about 14 us less per solve (n = 1000, 42 solves:
+// 6.00 -> 5.40 ms; n = 6001 FP16: 374 -> 307 us for the pair).  All LDS matrices have row stride LS (odd: a
+// column's accesses fall into different banks).
+template <int BS> struct lds_stride { static constexpr int LS = BS + 1; };
+
+// one 16 x 16 fragment of P Q, K deep: P at Pm (row stride LS), Q at Qm
+template <typename V, int K, int LS>
+__device__ __forceinline__ typename mfma16x4<V>::acc_t frag_mul(const V *__restrict__ Pm,
+                                                                const V *__restrict__ Qm, int lane)
 {
-    // each row's sum in four interleaved partial sums, so the dependent
-    // chain is about a quarter as long
-    V xi[BS];
-    if constexpr (LOWER) {
+    const int r = lane & 15, g = lane >> 4;
+    typename mfma16x4<V>::acc_t acc = {0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < BS; ++i) {
-            V a[4] = {lane == i ? (V)1 : (V)0, 0, 0, 0};
+    for (int k = 0; k < K; k += 4)
+        acc = mfma16x4<V>::op(Pm[r * LS + k + g], Qm[(k + g) * LS + r], acc);
+    return acc;
+}
+// acc -= P T with T a fragment as an earlier product left it: register q of
+// lane l holds row row(l, q) of T, so step q takes that k in both operands
+template <typename V, int LS>
+__device__ __forceinline__ void frag_sub(typename mfma16x4<V>::acc_t &acc, const V *__restrict__ Pm,
+                                         const typename mfma16x4<V>::acc_t &t, int lane)
+{
 #pragma unroll
-            for (int k = 0; k < i; ++k) a[k & 3] -= Dr[i * BS + k] * xi[k];
-            xi[i] = (a[0] + a[1]) + (a[2] + a[3]);
-        }
-    } else {
+    for (int q = 0; q < 4; ++q)
+        acc = mfma16x4<V>::op(-Pm[(lane & 15) * LS + mfma16x4<V>::row(lane, q)], t[q], acc);
+}
+template <typename V, int LS>
+__device__ __forceinline__ void frag_store(V *__restrict__ X, const typename mfma16x4<V>::acc_t &a,
+                                           int lane)
+{
 #pragma unroll
-        for (int i = BS - 1; i >= 0; --i) {
-            V a[4] = {lane == i ? (V)1 : (V)0, 0, 0, 0};
-#pragma unroll
-            for (int k = i + 1; k < BS; ++k) a[k & 3] -= Dr[i * BS + k] * xi[k];
-            xi[i] = ((a[0] + a[1]) + (a[2] + a[3])) * rd[i];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < BS; ++i) Di[i * (BS + 1) + lane] = xi[i];
+    for (int q = 0; q < 4; ++q) X[mfma16x4<V>::row(lane, q) * LS + (lane & 15)] = a[q];
 }
 
-// Mx = Di Eb (BS x BS each), all four wavefronts: lane = row, wavefront wv
-// = columns 16 wv .. 16 wv + 15.  Di stride BS + 1, Eb stride BS, Mx stride BS + 1.
-template <typename V, int BS>
-__device__ __forceinline__ void diag_times_tile(const V *__restrict__ Di, const V *__restrict__ Eb,
-                                                V *__restrict__ Mx, int lane, int wv)
+// Di = D^{-1} (LOWER: unit lower; else upper with reciprocals rd of its
+// diagonal), then Dr = Di Eb if `mx`.  All 256 threads; Di zeroed and Dr
+// (zero on and beyond the diagonal's wrong side) and Eb stored by the caller,
+// without a barrier since.  Ends without a barrier.
+template <typename V, int BS, bool LOWER>
+__device__ __forceinline__ void diag_inverse_mx(V *__restrict__ Dr, const V *__restrict__ rd,
+                                                const V *__restrict__ Eb, V *__restrict__ Di,
+                                                bool mx, int lane, int wv)
 {
-    constexpr int CW = BS / 4;
-    V m[CW];
+    static_assert(BS == 64, "four wavefronts, one 16-row block each");
+    constexpr int LS = lds_stride<BS>::LS;
+    typedef typename mfma16x4<V>::acc_t acc_t;
+    __syncthreads();
+    {  // 16 x 16 blocks, lane & 15 = column of the inverse
+        const V *D = Dr + 16 * wv * (LS + 1);
+        const int c = lane & 15;
+        V xi[16];
 #pragma unroll
-    for (int c = 0; c < CW; ++c) m[c] = 0;
-#pragma unroll 8
-    for (int k = 0; k < BS; ++k) {
-        const V d = Di[lane * (BS + 1) + k];
+        for (int s = 0; s < 16; ++s) {
+            const int i = LOWER ? s : 15 - s;
+            V a[2] = {c == i ? (V)1 : (V)0, 0};
 #pragma unroll
-        for (int c = 0; c < CW; ++c) m[c] += d * Eb[k * BS + wv * CW + c];
+            for (int u = 0; u < s; ++u) {
+                const int k = LOWER ? u : 15 - u;
+                a[u & 1] -= D[i * LS + k] * xi[k];
+            }
+            xi[i] = a[0] + a[1];
+            if constexpr (!LOWER) xi[i] *= rd[16 * wv + i];
+        }
+        if (lane < 16) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) Di[(16 * wv + i) * LS + 16 * wv + c] = xi[i];
+        }
     }
+    __syncthreads();
+    constexpr int A = LOWER ? 1 : 0, B = 1 - A;  // row and column half of the coupling block
+    if (wv < 2) {                                // 16 -> 32, one pair of blocks per wavefront
+        const int ra = 32 * wv + 16 * A, cb = 32 * wv + 16 * B;
+        const acc_t t = frag_mul<V, 16, LS>(Dr + ra * LS + cb, Di + cb * LS + cb, lane);
+        acc_t x = {0, 0, 0, 0};
+        frag_sub<V, LS>(x, Di + ra * LS + ra, t, lane);
+        frag_store<V, LS>(Di + ra * LS + cb, x, lane);
+    }
+    __syncthreads();
+    {  // 32 -> 64, one 16 x 16 fragment of the coupling block per wavefront
+        const int ra = 32 * A, cb = 32 * B, i = wv >> 1, j = wv & 1;
+        acc_t x = {0, 0, 0, 0};
 #pragma unroll
-    for (int c = 0; c < CW; ++c) Mx[lane * (BS + 1) + wv * CW + c] = m[c];
+        for (int h = 0; h < 2; ++h) {
+            const acc_t t = frag_mul<V, 32, LS>(Dr + (ra + 16 * h) * LS + cb,
+                                                Di + cb * LS + cb + 16 * j, lane);
+            frag_sub<V, LS>(x, Di + (ra + 16 * i) * LS + ra + 16 * h, t, lane);
+        }
+        frag_store<V, LS>(Di + (ra + 16 * i) * LS + cb + 16 * j, x, lane);
+    }
+    __syncthreads();
+    if (!mx) return;
+    // Mx: 16 columns per wavefront; the inverse's zero 16 x 16 blocks left out
+    const int r = lane & 15, g = lane >> 4;
+    V e[BS / 4];
+#pragma unroll
+    for (int s = 0; s < BS / 4; ++s) e[s] = Eb[(4 * s + g) * LS + 16 * wv + r];
+#pragma unroll
+    for (int i = 0; i < BS / 16; ++i) {
+        acc_t m = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = LOWER ? 0 : 4 * i; s < (LOWER ? 4 * (i + 1) : BS / 4); ++s)
+            m = mfma16x4<V>::op(Di[(16 * i + r) * LS + 4 * s + g], e[s], m);
+        frag_store<V, LS>(Dr + 16 * i * LS + 16 * wv, m, lane);
+    }
 }
 
 // sum_c r[c] v[c] with v held one value per lane, four independent partial sums.
@@ -313,14 +385,15 @@ __global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restri
                                                     int *__restrict__ flags, int round_out)
 {
     static_assert(BS == 64, "a wavefront spans one tile");
+    constexpr int LS = lds_stride<BS>::LS, PT = BS / 4;
     __shared__ int s_blk;
-    __shared__ __attribute__((aligned(16))) V Dr[BS * (BS + 1)];  // D (stride BS), then Mx (stride BS + 1)
-    __shared__ __attribute__((aligned(16))) V Eb[BS * BS];        // L_{b,b-1}
-    __shared__ V Di[BS * (BS + 1)];                               // D^{-1}
+    __shared__ V Dr[BS * LS];     // D, then Mx
+    __shared__ V Eb[BS * LS];     // L_{b,b-1}
+    __shared__ V Di[BS * LS];     // D^{-1}
     __shared__ V part[4][BS];
     __shared__ __attribute__((aligned(16))) V vb[4][BS];  // each wavefront's broadcast vector
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    if (tid == 0) s_blk = __hip_atomic_fetch_add(&sync[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) s_blk = take_ticket(sync, epoch, gridDim.x);
     __syncthreads();
     const int blk = s_blk;
     uint64_t *tags = tag_words(sync);
@@ -333,16 +406,26 @@ __global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restri
     V fv[BS], fvn[BS];
     lane_word<V> cur, nxt;
     const int last = blk - 1;  // tiles jb < last go through the loop
-    for (int e = tid; e < BS * BS; e += 256) {
-        const int i = e % BS, j = e / BS;
-        const bool in = r0 + i < n;
-        Dr[i * BS + j] = (j < i && in) ? (V)to_f32(LU[(r0 + i) + (r0 + j) * lda]) : (V)0;
-        if (blk > 0) Eb[i * BS + j] = in ? (V)to_f32(LU[(r0 + i) + (r0 - BS + j) * lda]) : (V)0;
+    {
+        // lane = row, columns wv, wv + 4, ...: all loads first (columns
+        // clamped in bounds), then the zeros and the stores to LDS
+        T d[PT], e[PT];
+#pragma unroll
+        for (int k = 0; k < PT; ++k)
+            d[k] = LU[rowc + std::min<int64_t>(r0 + wv + 4 * k, n - 1) * lda];
+        if (blk > 0) {
+#pragma unroll
+            for (int k = 0; k < PT; ++k) e[k] = LU[rowc + (r0 - BS + wv + 4 * k) * lda];
+        }
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const int j = wv + 4 * k;
+            Dr[lane * LS + j] = j < lane && rv ? (V)to_f32(d[k]) : (V)0;
+            Di[lane * LS + j] = 0;
+            if (blk > 0) Eb[lane * LS + j] = rv ? (V)to_f32(e[k]) : (V)0;
+        }
     }
-    __syncthreads();
-    if (wv == 0) diag_inverse<V, BS, true>(Dr, nullptr, Di, lane);
-    __syncthreads();
-    if (blk > 0) diag_times_tile<V, BS>(Di, Eb, Dr, lane, wv);
+    diag_inverse_mx<V, BS, true>(Dr, nullptr, Eb, Di, blk > 0, lane, wv);
     int jb = wv;
     if (jb < last) {
         load_tile_row<T, V, BS>(fv, LU, lda, rowc, (int64_t)jb * BS, n);
@@ -401,16 +484,17 @@ __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restri
                                                     int round_out)
 {
     static_assert(BS == 64, "a wavefront spans one tile");
+    constexpr int LS = lds_stride<BS>::LS, PT = BS / 4;
     __shared__ int s_blk;
-    __shared__ __attribute__((aligned(16))) V Dr[BS * (BS + 1)];  // D (stride BS), then Mx (stride BS + 1)
-    __shared__ __attribute__((aligned(16))) V Eb[BS * BS];        // U_{b,b+1}
-    __shared__ V Di[BS * (BS + 1)];                               // D^{-1}
+    __shared__ V Dr[BS * LS];     // D, then Mx
+    __shared__ V Eb[BS * LS];     // U_{b,b+1}
+    __shared__ V Di[BS * LS];     // D^{-1}
     __shared__ V rd[BS];
     __shared__ V part[4][BS];
     __shared__ __attribute__((aligned(16))) V vb[4][BS];  // each wavefront's broadcast vector
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int nb = (int)((n + BS - 1) / BS);
-    if (tid == 0) s_blk = nb - 1 - __hip_atomic_fetch_add(&sync[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) s_blk = nb - 1 - take_ticket(sync, epoch, gridDim.x);
     __syncthreads();
     const int blk = s_blk;
     uint64_t *tags = tag_words(sync);
@@ -424,21 +508,28 @@ __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restri
     lane_word<V> cur, nxt;
     const int next = blk + 1;  // tiles jb > next go through the loop
     const bool has_next = next < nb;
-    for (int e = tid; e < BS * BS; e += 256) {
-        const int i = e % BS, j = e / BS;
-        const bool in = r0 + i < n && r0 + j < n;
-        const V u = in ? (V)to_f32(LU[(r0 + i) + (r0 + j) * lda]) : (V)0;
-        Dr[i * BS + j] = j > i ? u : (V)0;
-        if (i == j) rd[i] = in ? (V)1 / u : (V)1;
+    {
+        T d[PT], e[PT];
+#pragma unroll
+        for (int k = 0; k < PT; ++k)
+            d[k] = LU[rowc + std::min<int64_t>(r0 + wv + 4 * k, n - 1) * lda];
         if (has_next) {
-            const bool in2 = r0 + i < n && r0 + BS + j < n;
-            Eb[i * BS + j] = in2 ? (V)to_f32(LU[(r0 + i) + (r0 + BS + j) * lda]) : (V)0;
+#pragma unroll
+            for (int k = 0; k < PT; ++k)
+                e[k] = LU[rowc + std::min<int64_t>(r0 + BS + wv + 4 * k, n - 1) * lda];
+        }
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const int j = wv + 4 * k;
+            const bool in = rv && r0 + j < n;
+            const V u = in ? (V)to_f32(d[k]) : (V)0;
+            Dr[lane * LS + j] = j > lane ? u : (V)0;
+            if (j == lane) rd[j] = in ? (V)1 / u : (V)1;
+            Di[lane * LS + j] = 0;
+            if (has_next) Eb[lane * LS + j] = rv && r0 + BS + j < n ? (V)to_f32(e[k]) : (V)0;
         }
     }
-    __syncthreads();
-    if (wv == 0) diag_inverse<V, BS, false>(Dr, rd, Di, lane);
-    __syncthreads();
-    if (has_next) diag_times_tile<V, BS>(Di, Eb, Dr, lane, wv);
+    diag_inverse_mx<V, BS, false>(Dr, rd, Eb, Di, has_next, lane, wv);
     int jb = nb - 1 - wv;
     if (jb > next) {
         load_tile_row<T, V, BS>(fv, LU, lda, rowc, (int64_t)jb * BS, n);
@@ -480,8 +571,6 @@ __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restri
     }
 }
 
-__global__ void k_zero_ticket(int *sync) { sync[0] = 0; }
-
 // ticket (4 ints, keeps the tag words 16-byte aligned) + 2 tag words per entry
 size_t trsv_sync_ints(int64_t n) { return (size_t)(4 + 4 * n); }
 
@@ -491,7 +580,6 @@ static hipError_t trsv_lower_t(int64_t n, const void *LU, int64_t lda, const int
                                hipStream_t s, int round_out = 0)
 {
     const unsigned nb = (unsigned)((n + TRSV_BS - 1) / TRSV_BS);
-    hipLaunchKernelGGL(k_zero_ticket, dim3(1), dim3(1), 0, s, sync);
     hipLaunchKernelGGL((k_trsv_lower<T, V, TRSV_BS>), dim3(nb), dim3(256), 0, s, n, (const T *)LU,
                        lda, perm, b, y, sync, epoch, flags, round_out);
     return hipGetLastError();
@@ -503,7 +591,6 @@ static hipError_t trsv_upper_t(int64_t n, const void *LU, int64_t lda, const V *
                                hipStream_t s, int round_out = 0)
 {
     const unsigned nb = (unsigned)((n + TRSV_BS - 1) / TRSV_BS);
-    hipLaunchKernelGGL(k_zero_ticket, dim3(1), dim3(1), 0, s, sync);
     hipLaunchKernelGGL((k_trsv_upper<T, V, TRSV_BS>), dim3(nb), dim3(256), 0, s, n, (const T *)LU,
                        lda, y, colscale, x, sync, epoch, flags, round_out);
     return hipGetLastError();

@@ -42,6 +42,29 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// 16x16x4 matrix-core product in FP32 or FP64: lane l supplies A(l & 15, l >> 4)
+// and B(l >> 4, l & 15).
+template <typename T> struct mfma16x4;
+// Output layout of the 16x16 fragment: lane l holds column l & 15; register q
+// holds row 4 (l >> 4) + q for the FP32 instruction and row (l >> 4) + 4 q for
+// the FP64 one (checked on gfx950 with an in-bounds probe).
+template <> struct mfma16x4<float> {
+    typedef f32x4 acc_t;
+    static __device__ __forceinline__ int row(int lane, int q) { return 4 * (lane >> 4) + q; }
+    static __device__ __forceinline__ acc_t op(float a, float b, acc_t c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct mfma16x4<double> {
+    typedef f64x4 acc_t;
+    static __device__ __forceinline__ int row(int lane, int q) { return (lane >> 4) + 4 * q; }
+    static __device__ __forceinline__ acc_t op(double a, double b, acc_t c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+
 // compute type of the factorisation arithmetic for a storage type
 template <typename T> struct compute_of { typedef float type; };
 template <> struct compute_of<double> { typedef double type; };

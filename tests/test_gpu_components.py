@@ -381,6 +381,26 @@ def test_getrs_with_oracle_factors(env, prec, n):
     assert np.linalg.norm(x - x_ref) / np.linalg.norm(x_ref) < tol
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 32, 33, 48, 49, 80, 128, 145])
+def test_getrs_fragment_edges_with_oracle_factors(env, prec, n):
+    """The diagonal blocks' inverses are built from 16 x 16 pieces: sizes at
+    the edges of the pieces, in the first block and in a partial last one.
+    Diagonally dominant, so the bound is a few roundings of the solve's type."""
+    n3p, torch = env
+    A = diag_dominant(n, 60 + n)
+    b = np.random.default_rng(n).standard_normal(n)
+    LU, piv, _ = O.getrf(A)
+    dt = {"fp64": torch.float64, "fp32": torch.float32, "bf16": torch.bfloat16}[prec]
+    LUt = to_cm(torch, LU, dt)
+    LU_r = from_cm(LUt)
+    x_ref = O.getrs(LU_r, piv, b if prec == "fp64" else b.astype(np.float32).astype(np.float64))
+    bt = torch.from_numpy(b).to("cuda", torch.float64 if prec == "fp64" else torch.float32)
+    n3p.getrs(LUt, torch.from_numpy(piv).cuda(), bt)
+    x = bt.double().cpu().numpy()
+    assert np.linalg.norm(x - x_ref) / np.linalg.norm(x_ref) < 16 * (2.0 ** -53 if prec == "fp64" else U32)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp16"])
 def test_getrs_many_blocks_with_oracle_factors(env, prec):
     """33 row blocks with a ragged last one, diagonally dominant so that the
