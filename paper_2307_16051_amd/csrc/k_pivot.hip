@@ -3,15 +3,18 @@
 // half-precision factorisation of Section 2), taken when the no-interchange
 // attempt of k_getrf.hip finds that partial pivoting would interchange rows.
 //
-// Per 64-column leaf: k_pivot_coop (pivot search, interchanges inside the
-// leaf, multipliers, ipiv) and k_gather_u12 (the leaf's interchanges on the
-// rest of its outer block, and its U row block there).  Per outer block:
+// Per 64-column leaf: k_pivot_coop, or k_pivot_one for at most 4096 rows
+// (pivot search, interchanges inside the leaf, multipliers, ipiv) and
+// k_gather_u12 (the leaf's interchanges on the rest of its outer block, its U
+// row block there, and the store of k_pivot_one's panel).  Per outer block:
 // k_compose_lists and k_gather_block (the block's interchanges, composed into
 // one list, on all other columns),
 // k_lt_rebuild (the block's L transposed), k_u12 (U row blocks right of the
 // block).  The Schur-complement updates reuse the matrix-core GEMMs of
 // k_getrf.hip.
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "n3p_internal.hpp"
 
@@ -533,6 +536,55 @@ struct PcState {
     }
 };
 
+// One wavefront: ipiv, and the leaf's 64 interchanges (position pivs[t] with
+// position t) composed into one list of (dest, src) row moves: entry e < 64 is
+// panel row e (lane e, val_lo); rows >= 64 that take part get entries 64 + i
+// (lane i, key_hi / val_hi).
+__device__ __forceinline__ void leaf_list(const int *pivs, int lane, int64_t c0,
+                                          int *__restrict__ list, int32_t *__restrict__ ipiv)
+{
+    constexpr int L = NB_LEAF;
+    int val_lo = lane, key_hi = -1, val_hi = -1, nh = 0;
+    for (int t = 0; t < L; ++t) {
+        const int p = pivs[t];
+        if (p == t) continue;
+        int e = p;
+        if (p >= L) {
+            const unsigned long long b = __ballot(key_hi == p);
+            if (b) {
+                e = L + (int)__builtin_ctzll(b);
+            } else {
+                e = L + nh;
+                if (lane == nh) { key_hi = p; val_hi = p; }
+                ++nh;
+            }
+        }
+        const int vt = __builtin_amdgcn_readlane(val_lo, t);
+        const int ve = e < L ? __builtin_amdgcn_readlane(val_lo, e) : __builtin_amdgcn_readlane(val_hi, e - L);
+        if (lane == t) val_lo = ve;
+        if (e < L) {
+            if (lane == e) val_lo = vt;
+        } else if (lane == e - L) {
+            val_hi = vt;
+        }
+    }
+    const bool m0 = val_lo != lane, m1 = lane < nh && val_hi != key_hi;
+    const unsigned long long b0 = __ballot(m0), b1 = __ballot(m1);
+    const int n0 = __popcll(b0);
+    if (m0) {
+        const int i = __builtin_amdgcn_mbcnt_hi((unsigned)(b0 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b0, 0));
+        list[1 + 2 * i] = (int)c0 + lane;
+        list[2 + 2 * i] = (int)c0 + val_lo;
+    }
+    if (m1) {
+        const int i = n0 + __builtin_amdgcn_mbcnt_hi((unsigned)(b1 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b1, 0));
+        list[1 + 2 * i] = (int)c0 + key_hi;
+        list[2 + 2 * i] = (int)c0 + val_hi;
+    }
+    if (lane == 0) list[0] = n0 + __popcll(b1);
+    ipiv[c0 + lane] = (int32_t)(c0 + pivs[lane]);
+}
+
 template <typename T, typename CT>
 __global__ __launch_bounds__(pc_cfg<CT>::TH) void k_pivot_coop(int64_t Np, int64_t c0, int64_t k0,
                                                            T *__restrict__ A, int64_t lda,
@@ -632,50 +684,359 @@ __global__ __launch_bounds__(pc_cfg<CT>::TH) void k_pivot_coop(int64_t Np, int64
     }
     if (bad) set_flag(&flags[FLAG_NONFINITE], 1);
 
-    // --- workgroup 0: ipiv, and the 64 interchanges composed into one list of
-    // (dest, src) row moves: entry e < 64 is panel row e (lane e, val_lo); rows
-    // >= 64 that take part get entries 64 + i (lane i, key_hi/val_hi).
+    // --- workgroup 0: ipiv and the leaf's list
     __syncthreads();
-    if (wg == 0 && wv == 0) {
-        int val_lo = lane, key_hi = -1, val_hi = -1, nh = 0;
-        for (int t = 0; t < L; ++t) {
-            const int p = pivs[t];
-            if (p == t) continue;
-            int e = p;
-            if (p >= L) {
-                const unsigned long long b = __ballot(key_hi == p);
-                if (b) {
-                    e = L + (int)__builtin_ctzll(b);
-                } else {
-                    e = L + nh;
-                    if (lane == nh) { key_hi = p; val_hi = p; }
-                    ++nh;
+    if (wg == 0 && wv == 0) leaf_list(pivs, lane, c0, list, ipiv);
+}
+
+// The same leaf by ONE workgroup, for panels of at most PO_MAX_ROWS rows: no
+// exchange between CUs, so a column costs one LDS barrier instead of a round
+// trip through memory.  What bounds it: per column a serial chain (two
+// reductions, a barrier, the pivot row through LDS, the division), and the
+// leaf's m x 64 x 64 / 2 multiply-adds on one CU.
+//
+// Rows stay where they were loaded (row t + nt r of the panel in slot r of
+// thread t); an interchange only changes the positions `pos` of two rows, and
+// the panel is stored by position afterwards (store_panel, on other CUs).
+// The leaf is taken in sub-panels of SW columns, SW x R values per thread in
+// registers; a sub-panel is loaded, gets the updates of the leaf's earlier
+// columns in column order (their multipliers, in the compute type, come from
+// the scratch, column-major; their U rows from LDS), and is then eliminated
+// column by column.  Per element these are the operations of k_pivot_coop in
+// the same order, so the factors and pivots are identical.
+//
+// Measured per leaf, against 235 us (FP32 compute) and 340 us (FP64) for
+// k_pivot_coop at these sizes: FP16 storage 68 us up to 512 rows, 83 up to
+// 1024, 115 up to 2048, about 190 up to 4096; FP64 88, 110, 160, 295.  A
+// column takes 0.6 to 1.7 us; beyond 2048 rows the multiply-adds of one CU
+// set the time (0.42 us per earlier column and sub-panel), and past 4096 the
+// registers end, which is where the line to k_pivot_coop lies.
+constexpr int PO_MAX_ROWS = 4096, PO_NT = 512;
+// scratch of one panel: its values in the compute type, column-major (row
+// stride 1), then each row's position, then the pivots' rows
+template <typename CT> struct PoScratch {
+    CT *v;
+    int *pos, *prow;
+    __host__ __device__ explicit PoScratch(void *base)
+        : v((CT *)base), pos((int *)(v + (size_t)NB_LEAF * PO_MAX_ROWS)), prow(pos + PO_MAX_ROWS)
+    {
+    }
+    static constexpr size_t bytes = (size_t)NB_LEAF * PO_MAX_ROWS * sizeof(CT) + (PO_MAX_ROWS + NB_LEAF) * 4;
+    __device__ __forceinline__ CT &at(int k, int row) const { return v[k * PO_MAX_ROWS + row]; }
+};
+
+// f(0), f(1), ... f(N - 1), each with its index as a compile-time constant
+// (register arrays stay in registers however long the body)
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_const(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// The wavefront's largest a (none of them NaN), uniform: rows of 16 by DPP,
+// then across the rows by row broadcasts.
+template <int CTRL> __device__ __forceinline__ float max_step(float a)
+{
+    // non-negative floats order as their bits do, -1 (no candidate) below all
+    const int x = __float_as_int(a);
+    return __int_as_float(max(x, dpp_i<CTRL>(x)));
+}
+template <int CTRL> __device__ __forceinline__ double max_step(double a)
+{
+    double r;
+    const double o = dpp_v<CTRL>(a);
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(o));
+    return r;
+}
+template <typename CT> __device__ __forceinline__ CT wave_max(CT a)
+{
+    a = max_step<0xB1>(a);   // quad_perm [1,0,3,2]
+    a = max_step<0x4E>(a);   // quad_perm [2,3,0,1]
+    a = max_step<0x141>(a);  // row_half_mirror
+    a = max_step<0x140>(a);  // row_mirror
+    a = max_step<0x142>(a);  // row_bcast:15
+    a = max_step<0x143>(a);  // row_bcast:31
+    return lane_read(a, 63);
+}
+// The smallest i among the lanes, uniform; one lane with i != none is the
+// common case.
+__device__ __forceinline__ int wave_min(int i, int none)
+{
+    const unsigned long long b = __ballot(i != none);
+    if (__popcll(b) == 1) return __builtin_amdgcn_readlane(i, (int)__builtin_ctzll(b));
+    i = min(i, dpp_i<0xB1>(i));
+    i = min(i, dpp_i<0x4E>(i));
+    i = min(i, dpp_i<0x141>(i));
+    i = min(i, dpp_i<0x140>(i));
+    i = min(i, dpp_i<0x142>(i));
+    i = min(i, dpp_i<0x143>(i));
+    return __builtin_amdgcn_readlane(i, 63);
+}
+
+template <typename T, typename CT, int SW, int R>
+__global__ __launch_bounds__(PO_NT) void k_pivot_one(int64_t Np, int64_t c0, const T *__restrict__ A,
+                                                     int64_t lda, int32_t *__restrict__ ipiv,
+                                                     void *__restrict__ scratch,
+                                                     int *__restrict__ list, int *__restrict__ flags)
+{
+    constexpr int L = NB_LEAF, NWV = PO_NT / 64, NE = 16 / sizeof(CT), NONE = 0x7fffffff;
+    constexpr int CPW = SW / NWV;                // U columns per wavefront
+    constexpr int KU = R >= 8 ? 2 : 16 / R;      // earlier columns in flight
+    typedef typename cvec16<CT>::type CV;
+    static_assert(L % SW == 0 && SW % NE == 0 && SW % NWV == 0, "whole sub-panels and LDS vectors");
+    static_assert(NWV == 8, "the wavefronts' candidates are reduced in eight lanes");
+    __shared__ CT red_v[2][NWV];
+    __shared__ int red_i[2][NWV], red_r[2][NWV];
+    __shared__ __attribute__((aligned(16))) CT crow[2][NWV][SW];  // each wavefront's candidate row
+    __shared__ __attribute__((aligned(16))) CT us[L][SW];         // U rows of the sub-panel's columns
+    __shared__ CT lp[L][L + 1];                                   // the pivot rows' multipliers
+    __shared__ int pivs[L], prow[L];  // column k: the pivot's position, and its row
+    __shared__ int moves;
+    if (threadIdx.x == 0) moves = 0;
+    if (block_flag(&flags[FLAG_TIMEOUT])) return;
+    const PoScratch<CT> sc(scratch);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = (int)(Np - c0);
+    int row[R], pos[R];
+    CT v[R][SW];
+    uint64_t zero = 0;  // columns with a zero pivot: no multipliers, no update
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        row[r] = tid + PO_NT * r;
+        pos[r] = row[r] < m ? row[r] : -1;  // -1: no row, never a candidate
+    }
+#pragma unroll 1
+    for (int s0 = 0; s0 < L; s0 += SW) {
+        // --- U rows of the finished pivots in these columns: CPW columns per
+        // wavefront, lane = finished pivot, substitution in column order
+        if (s0 > 0) {
+            CT y[CPW];
+            const T *src = A + c0 + prow[lane < s0 ? lane : 0] + (c0 + s0 + wv * CPW) * lda;
+#pragma unroll
+            for (int j = 0; j < CPW; ++j) y[j] = (CT)to_f32(src[j * lda]);
+            for (int k0 = 0; k0 < s0; k0 += SW) {
+                CT l[SW];
+#pragma unroll
+                for (int k = 0; k < SW; ++k) l[k] = lane > k0 + k ? lp[lane][k0 + k] : (CT)0;
+#pragma unroll
+                for (int k = 0; k < SW; ++k) {
+#pragma unroll
+                    for (int j = 0; j < CPW; ++j) {
+                        const CT yk = lane_read(y[j], k0 + k);
+                        if (!((zero >> (k0 + k)) & 1) && lane > k0 + k) y[j] = fma(-l[k], yk, y[j]);
+                    }
                 }
             }
-            const int vt = __builtin_amdgcn_readlane(val_lo, t);
-            const int ve = e < L ? __builtin_amdgcn_readlane(val_lo, e) : __builtin_amdgcn_readlane(val_hi, e - L);
-            if (lane == t) val_lo = ve;
-            if (e < L) {
-                if (lane == e) val_lo = vt;
-            } else if (lane == e - L) {
-                val_hi = vt;
+            if (lane < s0) {
+#pragma unroll
+                for (int j = 0; j < CPW; ++j) us[lane][wv * CPW + j] = y[j];
             }
         }
-        const bool m0 = val_lo != lane, m1 = lane < nh && val_hi != key_hi;
-        const unsigned long long b0 = __ballot(m0), b1 = __ballot(m1);
-        const int n0 = __popcll(b0);
-        if (m0) {
-            const int i = __builtin_amdgcn_mbcnt_hi((unsigned)(b0 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b0, 0));
-            list[1 + 2 * i] = (int)c0 + lane;
-            list[2 + 2 * i] = (int)c0 + val_lo;
+        // --- the sub-panel's columns of every row
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const T *src = A + (c0 + (row[r] < m ? row[r] : 0)) + (c0 + s0) * lda;
+#pragma unroll
+            for (int j = 0; j < SW; ++j) v[r][j] = (CT)to_f32(src[j * lda]);
         }
-        if (m1) {
-            const int i = n0 + __builtin_amdgcn_mbcnt_hi((unsigned)(b1 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b1, 0));
-            list[1 + 2 * i] = (int)c0 + key_hi;
-            list[2 + 2 * i] = (int)c0 + val_hi;
+        __syncthreads();
+        // --- the earlier columns' updates, in order; the next KU columns'
+        // multipliers are requested before the current ones are used
+        if (s0 > 0) {
+            CT l[KU][R], ln[KU][R];
+#pragma unroll
+            for (int u = 0; u < KU; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) l[u][r] = sc.at(u, row[r]);
+#pragma unroll 1
+            for (int k0 = 0; k0 < s0; k0 += KU) {
+                const int kn = k0 + KU < s0 ? k0 + KU : k0;
+#pragma unroll
+                for (int u = 0; u < KU; ++u)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) ln[u][r] = sc.at(kn + u, row[r]);
+#pragma unroll
+                for (int u = 0; u < KU; ++u) {
+                    if ((zero >> (k0 + u)) & 1) continue;
+#pragma unroll
+                    for (int q = 0; q < SW; q += NE) {
+                        const CV x = *(const CV *)&us[k0 + u][q];
+#pragma unroll
+                        for (int e = 0; e < NE; ++e)
+#pragma unroll
+                            for (int r = 0; r < R; ++r) v[r][q + e] = fma(-l[u][r], x[e], v[r][q + e]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < KU; ++u)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) l[u][r] = ln[u][r];
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (pos[r] >= 0 && pos[r] < s0) {  // a finished pivot row: its U entries
+#pragma unroll
+                    for (int q = 0; q < SW; q += NE) {
+                        const CV x = *(const CV *)&us[pos[r]][q];
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) v[r][q + e] = x[e];
+                    }
+                }
+            }
         }
-        if (lane == 0) list[0] = n0 + __popcll(b1);
-        ipiv[c0 + lane] = (int32_t)(c0 + pivs[lane]);
+        // --- the sub-panel's own columns
+        const auto column = [&](auto J) __attribute__((always_inline)) {
+            constexpr int j = decltype(J)::value, par = j & 1;
+            const int k = s0 + j;
+            // this wavefront's candidate: the largest magnitude (NaN counts as
+            // 0; its store reports it), then the lowest position that has it
+            CT best = (CT)-1;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const CT a = fabs(v[r][j]);
+                if (pos[r] >= k) {
+                    if (!(best >= (CT)0)) best = (CT)0;
+                    if (a > best) best = a;
+                }
+            }
+            const CT mx = wave_max(best);
+            int bi = NONE;
+            if (mx > (CT)0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (fabs(v[r][j]) == mx && pos[r] >= k) bi = min(bi, pos[r]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (pos[r] >= k) bi = min(bi, pos[r]);
+            }
+            const int wb = wave_min(bi, NONE);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (pos[r] == wb) {  // one lane, one slot (positions are distinct): the candidate row
+#pragma unroll
+                    for (int q = j / NE * NE; q < SW; q += NE) {
+                        CV x;
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) x[e] = v[r][q + e];
+                        *(CV *)&crow[par][wv][q] = x;
+                    }
+                    red_r[par][wv] = row[r];
+                }
+            }
+            if (lane == 0) { red_v[par][wv] = mx; red_i[par][wv] = wb; }
+            __syncthreads();
+            // every wavefront takes the same decision among the eight (each
+            // half row of lanes holds them all)
+            const CT c = red_v[par][lane & 7];
+            const int ci = red_i[par][lane & 7];
+            CT cm = max_step<0xB1>(c);
+            cm = max_step<0x4E>(cm);
+            cm = max_step<0x141>(cm);
+            int p = c == cm ? ci : NONE;
+            const unsigned same = (unsigned)(__ballot(c == cm) & 0xff);
+            int w = __builtin_ctz(same);
+            if (same & (same - 1)) {  // equal magnitudes in several wavefronts
+                p = min(p, dpp_i<0xB1>(p));
+                p = min(p, dpp_i<0x4E>(p));
+                p = min(p, dpp_i<0x141>(p));
+                p = __builtin_amdgcn_readfirstlane(p);
+                w = __builtin_ctz((unsigned)(__ballot(ci == p) & 0xff));
+            } else {
+                p = __builtin_amdgcn_readlane(p, w);
+            }
+            CV x[SW / NE];
+#pragma unroll
+            for (int q = j / NE; q < SW / NE; ++q) x[q] = *(const CV *)&crow[par][w][q * NE];
+            const CT pk = x[j / NE][j % NE];
+            const bool nz = lane_read(pk, 0) != (CT)0;
+            if (!nz) zero |= 1ull << k;
+            if (tid == 0) {
+                pivs[k] = p;
+                prow[k] = red_r[par][w];
+                if (!nz) atomicCAS(&flags[FLAG_ZEROPIV], 0, (int)(c0 + k + 1));
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int q = pos[r];
+                pos[r] = q == p ? k : q == k ? p : q;
+            }
+            if (nz) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const CT l = v[r][j] / pk;
+                    if (pos[r] > k) {
+                        v[r][j] = l;
+#pragma unroll
+                        for (int q = j + 1; q < SW; ++q) v[r][q] = fma(-l, x[q / NE][q % NE], v[r][q]);
+                    }
+                }
+            }
+        };
+        for_each_const(column, std::make_integer_sequence<int, SW>{});
+        // --- the columns to the scratch; the new pivot rows' multipliers to LDS
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (pos[r] < 0) continue;
+#pragma unroll
+            for (int j = 0; j < SW; ++j) sc.at(s0 + j, row[r]) = v[r][j];
+            if (pos[r] >= s0 && pos[r] < s0 + SW) {
+#pragma unroll
+                for (int j = 0; j < SW; ++j) lp[pos[r]][s0 + j] = v[r][j];
+            }
+        }
+        __syncthreads();
+        if (s0 + SW < L) {
+            for (int k = s0 + wv; k < s0 + SW; k += NWV)
+                if (lane < s0) lp[k][lane] = sc.at(lane, prow[k]);
+            __syncthreads();
+        }
+    }
+    // the leaf's row moves: every row whose position changed (their order is
+    // immaterial; at most 64 pivots and the 64 rows they displaced)
+    if (tid < L) {
+        sc.prow[tid] = prow[tid];
+        ipiv[c0 + tid] = (int32_t)(c0 + pivs[tid]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (pos[r] < 0) continue;
+        sc.pos[row[r]] = pos[r];
+        if (pos[r] != row[r]) {
+            const int e = atomicAdd(&moves, 1);
+            list[1 + 2 * e] = (int)c0 + pos[r];
+            list[2 + 2 * e] = (int)c0 + row[r];
+        }
+    }
+    __syncthreads();
+    if (tid == 0) list[0] = moves;
+}
+
+// Rows [64 tile, 64 tile + 64) of a panel that k_pivot_one factored, from its
+// scratch into A by position, and those below the leaf into LT (through LDS:
+// a row of LT is contiguous).
+template <typename T, typename CT>
+__device__ __forceinline__ void store_panel(const PoScratch<CT> &sc, int tile, T *__restrict__ A,
+                                            int64_t lda, T *__restrict__ LT, int64_t c0, int64_t k0,
+                                            T (*__restrict__ buf)[NB_LEAF + 2], int *__restrict__ flags)
+{
+    constexpr int L = NB_LEAF;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, row = tile * 64 + lane;
+    const int pos = sc.pos[row];
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < L / 4; ++i) {
+        const int k = wv + 4 * i;
+        const T x = to_store_d<T>((double)sc.at(k, row));
+        bad |= !isfinite(to_f32(x));  // the stored value (FP16 overflows above 65504)
+        A[(c0 + pos) + (c0 + k) * lda] = x;
+        buf[lane][k] = x;
+    }
+    if (bad) set_flag(&flags[FLAG_NONFINITE], 1);
+    __syncthreads();
+    for (int i = wv; i < 64; i += 4) {
+        const int q = __builtin_amdgcn_readlane(pos, i);
+        if (q >= L) LT[(c0 + q) * (int64_t)NB_OUT + (c0 - k0) + lane] = buf[i][lane];
     }
 }
 
@@ -802,16 +1163,28 @@ __device__ __forceinline__ void load_l11(const T *__restrict__ A, int64_t lda, i
 // interchanges and then the substitution with the leaf's L11; columns left
 // of it only the interchanges.  Four columns per 256-thread workgroup: the
 // row moves of all four first (every read before any write), then one
-// wavefront per column.
-template <typename T>
+// wavefront per column.  ONE: the panel was factored by k_pivot_one and is
+// still in its scratch, from where L11 is read; the workgroups past the
+// columns' store it (one CU alone took 18 us for that at 1984 rows in FP16,
+// 55 us in FP64).
+template <typename T, bool ONE>
 __global__ __launch_bounds__(256) void k_gather_u12(T *__restrict__ A, int64_t lda,
                                                     const int *__restrict__ list, int64_t c0,
-                                                    int64_t k0, int64_t kend,
+                                                    int64_t k0, int64_t kend, T *__restrict__ LT,
+                                                    void *__restrict__ scratch,
                                                     int *__restrict__ flags)
 {
     typedef typename compute_of<T>::type CT;
     constexpr int L = NB_LEAF;
     __shared__ CT Lm[L][L + 1];
+    if constexpr (ONE) {
+        const int ncb = (int)((kend - k0 - L + 3) / 4);
+        if ((int)blockIdx.x >= ncb) {
+            __shared__ T buf[L][L + 2];
+            store_panel<T, CT>(PoScratch<CT>(scratch), (int)blockIdx.x - ncb, A, lda, LT, c0, k0, buf, flags);
+            return;
+        }
+    }
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int64_t ncol = kend - k0 - L, left = c0 - k0;
     const int64_t q0 = (int64_t)blockIdx.x * 4;
@@ -833,7 +1206,15 @@ __global__ __launch_bounds__(256) void k_gather_u12(T *__restrict__ A, int64_t l
             dst[h] = list[1 + 2 * e];
         }
     }
-    load_l11<T, CT>(A, lda, c0, Lm);
+    if constexpr (ONE) {
+        const PoScratch<CT> sc(scratch);
+        for (int i = t; i < L * L; i += 256) {
+            const int r = i % L, j = i / L;
+            Lm[r][j] = (CT)to_f32(to_store_d<T>((double)sc.at(j, sc.prow[r])));  // as stored
+        }
+    } else {
+        load_l11<T, CT>(A, lda, c0, Lm);
+    }
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -902,9 +1283,20 @@ static int64_t pc_words(int prec, int64_t Np)
            pmax * nwv * NB_LEAF * W;
 }
 
-size_t pivot_xch_bytes(int prec, int64_t Np)
+static size_t pc_exchange_bytes(int prec, int64_t Np)
 {
     return (size_t)pc_words(prec, Np) * 8 + ((size_t)PC_NLIST * PC_LIST_INTS + PC_COMP_INTS) * 4;
+}
+
+// exchange words and lists, then the one-workgroup panel's scratch
+size_t pivot_xch_bytes(int prec, int64_t Np)
+{
+    return (size_t)round_up((int64_t)pc_exchange_bytes(prec, Np), 256) +
+           (prec == N3P_FP64 ? PoScratch<double>::bytes : PoScratch<float>::bytes);
+}
+static void *po_scratch(int prec, int64_t Np, void *xch)
+{
+    return (char *)xch + round_up((int64_t)pc_exchange_bytes(prec, Np), 256);
 }
 
 static const int *pc_lists(int prec, int64_t Np, const void *xch)
@@ -914,7 +1306,7 @@ static const int *pc_lists(int prec, int64_t Np, const void *xch)
 
 hipError_t launch_pivot_reset(int prec, int64_t Np, void *xch, hipStream_t s)
 {
-    return launch_fill_i32((int *)xch, 0, (int64_t)(pivot_xch_bytes(prec, Np) / 4), s);
+    return launch_fill_i32((int *)xch, 0, (int64_t)(pc_exchange_bytes(prec, Np) / 4), s);
 }
 
 template <typename T, typename CT>
@@ -927,12 +1319,42 @@ static hipError_t pivot_coop_t(int64_t Np, int64_t c0, int64_t k0, void *A, int6
     return hipGetLastError();
 }
 
+// R rows per thread for m rows, as few as hold them; at eight FP64 rows the
+// sub-panels are half as wide, so that SW R values fit the registers
+template <typename T, typename CT>
+static hipError_t pivot_one_t(int64_t Np, int64_t c0, const void *A, int64_t lda, int32_t *ipiv,
+                              void *scratch, int *list, int *flags, hipStream_t s)
+{
+    const int64_t m = Np - c0;
+    constexpr int SW8 = sizeof(CT) == 8 ? 8 : 16;
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(PO_NT), 0, s, Np, c0, (const T *)A, lda, ipiv,
+                           scratch, list, flags);
+    };
+    if (m <= PO_NT) go(k_pivot_one<T, CT, 16, 1>);
+    else if (m <= 2 * PO_NT) go(k_pivot_one<T, CT, 16, 2>);
+    else if (m <= 4 * PO_NT) go(k_pivot_one<T, CT, 16, 4>);
+    else go(k_pivot_one<T, CT, SW8, 8>);
+    return hipGetLastError();
+}
+
 hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void *A, int64_t lda,
                              int32_t *ipiv, void *LT, void *xch, int *flags, hipStream_t s)
 {
     const int64_t rw = pc_rows_per_wg(prec), m = Np - c0;
     const int64_t P = (m + rw - 1) / rw, pmax = pc_pmax(prec, Np);
     if (m < NB_LEAF || m % NB_LEAF || P > PIVOT_MAX_WG) return hipErrorInvalidValue;
+    if (m <= PO_MAX_ROWS) {
+        void *sc = po_scratch(prec, Np, xch);
+        int *list = const_cast<int *>(pc_lists(prec, Np, xch)) + ((c0 - k0) / NB_LEAF) * PC_LIST_INTS;
+        switch (prec) {
+        case N3P_FP16: return pivot_one_t<f16, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
+        case N3P_BF16: return pivot_one_t<bf16, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
+        case N3P_FP32: return pivot_one_t<float, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
+        case N3P_FP64: return pivot_one_t<double, double>(Np, c0, A, lda, ipiv, sc, list, flags, s);
+        }
+        return hipErrorInvalidValue;
+    }
     switch (prec) {
     case N3P_FP16: return pivot_coop_t<f16, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, flags, s);
     case N3P_BF16: return pivot_coop_t<bf16, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, flags, s);
@@ -942,21 +1364,33 @@ hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void 
     return hipErrorInvalidValue;
 }
 
+// after launch_pivot_coop of the same leaf: also stores the panel it left in
+// its scratch (panels of at most PO_MAX_ROWS rows)
 hipError_t launch_gather_u12(int prec, int64_t Np, int64_t c0, int64_t k0, int64_t kend, void *A,
-                             int64_t lda, const void *xch, int *flags, hipStream_t s)
+                             int64_t lda, void *LT, void *xch, int *flags, hipStream_t s)
 {
-    const int64_t ncol = kend - k0 - NB_LEAF;
-    if (ncol <= 0) return hipSuccess;
+    const int64_t ncol = kend - k0 - NB_LEAF, m = Np - c0;
+    const bool one = m <= PO_MAX_ROWS;
+    const unsigned grid = (unsigned)((ncol + 3) / 4 + (one ? m / 64 : 0));
+    if (grid == 0) return hipSuccess;
+    if (m % 64) return hipErrorInvalidValue;
     const int *list = pc_lists(prec, Np, xch) + ((c0 - k0) / NB_LEAF) * PC_LIST_INTS;
-    const unsigned grid = (unsigned)((ncol + 3) / 4);
+    void *sc = po_scratch(prec, Np, xch);
+    const auto go = [&](auto t) {
+        typedef decltype(t) T;
+        if (one)
+            hipLaunchKernelGGL((k_gather_u12<T, true>), dim3(grid), dim3(256), 0, s, (T *)A, lda, list, c0, k0, kend, (T *)LT, sc, flags);
+        else
+            hipLaunchKernelGGL((k_gather_u12<T, false>), dim3(grid), dim3(256), 0, s, (T *)A, lda, list, c0, k0, kend, (T *)LT, sc, flags);
+        return hipGetLastError();
+    };
     switch (prec) {
-    case N3P_FP16: hipLaunchKernelGGL(k_gather_u12<f16>, dim3(grid), dim3(256), 0, s, (f16 *)A, lda, list, c0, k0, kend, flags); break;
-    case N3P_BF16: hipLaunchKernelGGL(k_gather_u12<bf16>, dim3(grid), dim3(256), 0, s, (bf16 *)A, lda, list, c0, k0, kend, flags); break;
-    case N3P_FP32: hipLaunchKernelGGL(k_gather_u12<float>, dim3(grid), dim3(256), 0, s, (float *)A, lda, list, c0, k0, kend, flags); break;
-    case N3P_FP64: hipLaunchKernelGGL(k_gather_u12<double>, dim3(grid), dim3(256), 0, s, (double *)A, lda, list, c0, k0, kend, flags); break;
-    default: return hipErrorInvalidValue;
+    case N3P_FP16: return go(f16());
+    case N3P_BF16: return go(bf16());
+    case N3P_FP32: return go(float());
+    case N3P_FP64: return go(double());
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_gather_block(int prec, int64_t Np, int64_t k0, int64_t kend, void *A,

@@ -291,7 +291,7 @@ int getrf_pivot(const FactorWs &f, hipStream_t s)
         auto lt = [&](int64_t row, int64_t col) { return (const void *)(LT + ((size_t)row * NB_OUT + (size_t)col) * es); };
         for (int64_t c0 = k0; c0 < kend; c0 += NB_LEAF) {
             HIPCHK(launch_pivot_coop(prec, Np, c0, k0, f.A, lda, f.ipiv, LT, f.xch, f.flags, s));
-            HIPCHK(launch_gather_u12(prec, Np, c0, k0, kend, f.A, lda, f.xch, f.flags, s));
+            HIPCHK(launch_gather_u12(prec, Np, c0, k0, kend, f.A, lda, LT, f.xch, f.flags, s));
             const int64_t c1 = c0 + NB_LEAF;
             if (c1 < kend) {
                 HIPCHK(launch_gemm_sub(prec, Np - c1, kend - c1, NB_LEAF, lt(c1, c0 - k0), NB_OUT,

@@ -234,7 +234,7 @@ hipError_t launch_pivot_reset(int prec, int64_t Np, void *xch, hipStream_t s);
 hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void *A, int64_t lda,
                              int32_t *ipiv, void *LT, void *xch, int *flags, hipStream_t s);
 hipError_t launch_gather_u12(int prec, int64_t Np, int64_t c0, int64_t k0, int64_t kend, void *A,
-                             int64_t lda, const void *xch, int *flags, hipStream_t s);
+                             int64_t lda, void *LT, void *xch, int *flags, hipStream_t s);
 hipError_t launch_gather_block(int prec, int64_t Np, int64_t k0, int64_t kend, void *A,
                                int64_t lda, const void *xch, hipStream_t s);
 hipError_t launch_lt_rebuild(int prec, int64_t Np, int64_t r0, int64_t k0, int64_t ncol,

@@ -345,6 +345,37 @@ def test_getrf_tie_break_lowest_row(env):
     assert ipiv.cpu().numpy()[0] == piv_ref[0] == 10
 
 
+@pytest.mark.parametrize("n", [448, 512, 576, 1024, 1088, 2048, 2112])
+def test_getrf_fp64_one_workgroup_panel_edges(env, n):
+    """Panels of at most 4096 rows are factored by one workgroup, one to eight
+    rows per thread by size: sizes around each change, in several sub-panels
+    and outer blocks, with the oracle's pivots."""
+    n3p, torch = env
+    A = random_matrix(n, 300 + n)
+    LU_ref, piv_ref, info_ref = O.getrf(A)
+    T = to_cm(torch, A, torch.float64)
+    ipiv, info = n3p.getrf(T)
+    assert info == info_ref == 0
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+    np.testing.assert_allclose(from_cm(T), LU_ref, rtol=1e-12, atol=1e-12 * np.abs(LU_ref).max())
+
+
+@pytest.mark.parametrize("rows", [[700, 130, 70, 1030], [1, 513, 514], [600, 88]])
+def test_getrf_tie_break_across_slots_and_wavefronts(env, rows):
+    """Equal magnitudes held by different rows of one thread, different lanes
+    and different wavefronts: the lowest row wins."""
+    n3p, torch = env
+    n = 1100
+    A = random_matrix(n, 4) * 0.1
+    A[:, 0] = 0.0
+    A[rows, 0] = [(-1.0) ** i * 3.0 for i in range(len(rows))]
+    T = to_cm(torch, A, torch.float64)
+    ipiv, info = n3p.getrf(T)
+    _, piv_ref, _ = O.getrf(A)
+    assert ipiv.cpu().numpy()[0] == piv_ref[0] == min(rows)
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+
+
 @pytest.mark.parametrize("prec", ["FP16", "BF16"])
 def test_mfma_rate_probe_does_its_work(env, prec):
     """The measurement helper: with every operand 1/32 each instruction adds
