@@ -68,6 +68,9 @@ int64_t padded(int64_t n) { return round_up(std::max<int64_t>(n, 1), NB_PAD); }
 struct FactorWs {
     int prec = 0;
     int64_t Np = 0;
+    // leading dimension actually factored: n rounded up to a leaf.  The rest
+    // of the padding is the identity and stays so, factors included
+    int64_t nf = 0;
     void *A = nullptr;        // Np x Np, ld Np
     void *LT = nullptr;       // Np x NB_OUT
     void *DG = nullptr;       // 2 x NB_LEAF^2
@@ -81,8 +84,9 @@ struct FactorWs {
 
 bool top_path(int prec) { return prec == N3P_FP16 || prec == N3P_BF16; }
 
-size_t factor_bytes(int prec, int64_t Np, Bump &b, FactorWs *f, char *base)
+size_t factor_bytes(int prec, int64_t n, Bump &b, FactorWs *f, char *base)
 {
+    const int64_t Np = padded(n);
     const size_t es = elem_size(prec);
     size_t oA = b.take((size_t)Np * Np * es);
     // the diagonal-square path double-buffers LT by block parity (the next
@@ -100,6 +104,7 @@ size_t factor_bytes(int prec, int64_t Np, Bump &b, FactorWs *f, char *base)
         f->inv = top_path(prec) ? (float *)(base + oInv) : nullptr;
         f->prec = prec;
         f->Np = Np;
+        f->nf = round_up(n, NB_LEAF);
         f->A = base + oA;
         f->LT = base + oLT;
         f->DG = base + oDG;
@@ -134,7 +139,7 @@ int read_flags(const FactorWs &f, hipStream_t s, int *h)
 int getrf_spec(const FactorWs &f, hipStream_t s)
 {
     const int prec = f.prec;
-    const int64_t Np = f.Np, lda = Np;
+    const int64_t Np = f.nf, lda = f.Np;
     const size_t es = elem_size(prec);
     char *A = (char *)f.A;
     char *LT = (char *)f.LT;
@@ -194,33 +199,37 @@ int getrf_spec(const FactorWs &f, hipStream_t s)
 // launch as the rest of block j's update (the rows below the square included).  LT alternates between
 // two buffers by block parity.  Publication tags are unique within a
 // factorisation (the area is cleared once at its start).
+// The last square ends with the last leaf that holds a column of the matrix
+// (20 us a leaf: n = 256 took eight leaves for four).  Up to two squares there
+// is no 256 x 256 update, so everything else ends there too; beyond, the
+// updates cover the padding (zeros), which keeps their tiles whole.
 int getrf_spec_top(const FactorWs &f, hipStream_t s)
 {
     const int prec = f.prec;
-    const int64_t Np = f.Np, lda = Np;
+    const int64_t nf = f.nf, Np = nf <= 2 * NB_OUT ? nf : f.Np, lda = f.Np;
     const size_t es = elem_size(prec);
     char *A = (char *)f.A;
-    char *LTb[2] = {(char *)f.LT, (char *)f.LT + (size_t)Np * NB_OUT * es};
+    char *LTb[2] = {(char *)f.LT, (char *)f.LT + (size_t)f.Np * NB_OUT * es};
     auto at = [&](int64_t i, int64_t j) { return (void *)(A + ((size_t)i + (size_t)j * lda) * es); };
     HIPCHK(launch_fill_i32((int *)f.pub, 0, (int64_t)(top_pub_words() * 2), s));
     uint32_t tag0 = 1;
-    HIPCHK(launch_top(prec, 0, (int)std::min<int64_t>(NB_OUT, Np), f.A, lda, LTb[0], f.pub, f.inv,
+    HIPCHK(launch_top(prec, 0, (int)std::min<int64_t>(NB_OUT, nf), f.A, lda, LTb[0], f.pub, f.inv,
                       f.flags, tag0, s));
     for (int64_t j = 0;; ++j) {
         const int64_t k0 = j * NB_OUT;
-        const int W = (int)std::min<int64_t>(NB_OUT, Np - k0);
+        const int W = (int)std::min<int64_t>(NB_OUT, nf - k0);
         const int64_t kend = k0 + W;
-        if (kend >= Np) break;
+        if (kend >= nf) break;
         char *LTj = LTb[j & 1];
         const void *Lbelow = LTj + (size_t)kend * NB_OUT * es;
         HIPCHK(launch_trsm(prec, Np, k0, W, f.A, lda, LTj, f.inv, f.flags, s));
-        const int W1 = (int)std::min<int64_t>(NB_OUT, Np - kend);
+        const int W1 = (int)std::min<int64_t>(NB_OUT, nf - kend);
         // the next square first; the rows below it join the fused update
         HIPCHK(launch_gemm_sub(prec, W1, W1, W, Lbelow, NB_OUT, at(k0, kend), lda,
                                at(kend, kend), lda, f.flags, true, s));
         tag0 += NB_OUT / NB_LEAF;
         const int64_t rest = Np - kend - W1;
-        if (rest > 0) {
+        if (kend + W1 < nf) {
             HIPCHK(launch_top_gemm(prec, kend, W1, f.A, lda, LTb[(j + 1) & 1], f.pub, f.inv, f.flags,
                                    tag0, Np - kend, rest, W, Lbelow, NB_OUT, at(k0, kend + W1),
                                    lda, at(kend, kend + W1), lda, rest, W1,
@@ -264,14 +273,15 @@ static hipStream_t pivot_side_stream()
 int getrf_pivot(const FactorWs &f, hipStream_t s)
 {
     const int prec = f.prec;
-    const int64_t Np = f.Np, lda = Np;
+    // larger sizes keep the padding, for the updates' 256-row tiles
+    const int64_t Np = f.nf <= 4096 ? f.nf : f.Np, lda = f.Np;
     const size_t es = elem_size(prec);
     char *A = (char *)f.A;
     auto at = [&](int64_t i, int64_t j) { return (void *)(A + ((size_t)i + (size_t)j * lda) * es); };
     // FP16/BF16: LT is double-buffered, so a block's update beyond the next
     // block can still read its LT while the next block's panel writes the other
     hipStream_t s2 = top_path(prec) ? pivot_side_stream() : nullptr;
-    char *LTb[2] = {(char *)f.LT, (char *)f.LT + (s2 ? (size_t)Np * NB_OUT * es : 0)};
+    char *LTb[2] = {(char *)f.LT, (char *)f.LT + (s2 ? (size_t)lda * NB_OUT * es : 0)};
     struct Ev {
         hipEvent_t e = nullptr;
         ~Ev()
@@ -423,7 +433,7 @@ size_t solve_layout(int64_t n, int prec, int ls, int m, int fftmode, SolveWs *w,
     Bump b;
     const int64_t Np = padded(n);
     FactorWs f;
-    factor_bytes(prec, Np, b, &f, base);
+    factor_bytes(prec, n, b, &f, base);
     const bool mf = (fftmode & 2) != 0;
     size_t oJ = mf ? 0 : b.take((size_t)n * n * 4);
     size_t oCS = b.take((size_t)Np * 4);
@@ -1129,7 +1139,7 @@ N3P_API size_t n3p_getrf_workspace_size(int64_t n, int prec)
 {
     if (n < 1 || !valid_prec(prec)) return 0;
     Bump b;
-    factor_bytes(prec, padded(n), b, nullptr, nullptr);
+    factor_bytes(prec, n, b, nullptr, nullptr);
     b.take(trsv_sync_ints(padded(n)) * 4);
     const int64_t Np = padded(n);
     const size_t vs = prec == N3P_FP64 ? 8 : 4;
@@ -1143,7 +1153,7 @@ static void getrs_layout(int64_t n, int prec, char *base, FactorWs *f, int **syn
                          void **xs, void **bc)
 {
     Bump b;
-    factor_bytes(prec, padded(n), b, f, base);
+    factor_bytes(prec, n, b, f, base);
     size_t os = b.take(trsv_sync_ints(padded(n)) * 4);
     const int64_t Np = padded(n);
     const size_t vs = prec == N3P_FP64 ? 8 : 4;

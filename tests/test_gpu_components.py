@@ -172,6 +172,28 @@ def test_getrf_half_several_outer_blocks_backward_error(env, prec, u, n):
     check_backward_error(A_in, from_cm(T), piv, u, stages, U32, eta_sub)
 
 
+@pytest.mark.parametrize("prec,u", [("fp16", U16), ("bf16", UBF), ("fp32", U32), ("fp64", 2.0 ** -53)])
+@pytest.mark.parametrize("kind", ["heq", "gaussian"])
+@pytest.mark.parametrize("n", [1, 64, 65, 300, 1025, 1217, 2049, 2241])
+def test_getrf_ends_with_the_last_leaf_of_the_matrix(env, prec, u, kind, n):
+    """The factorisation stops at n rounded up to a leaf of 64 columns inside
+    its padding (a multiple of 512): sizes with one to seven leaves in the
+    last square, alone and after full ones, without and with interchanges."""
+    n3p, torch = env
+    print("case getrf_last_leaf %s %s n=%d" % (prec, kind, n), flush=True)
+    dt = {"fp16": torch.float16, "bf16": torch.bfloat16, "fp32": torch.float32, "fp64": torch.float64}[prec]
+    A = O.heq_jacobian(np.ones(n), 0.99) if kind == "heq" else random_matrix(n, 19 + n)
+    T = to_cm(torch, A, dt)
+    A_in = from_cm(T)
+    ipiv, info = n3p.getrf(T)
+    assert info == 0
+    piv = ipiv.cpu().numpy()
+    if kind == "heq":
+        assert np.array_equal(piv, np.arange(n))
+    eta_sub = {"fp16": 2.0 ** -25, "bf16": 2.0 ** -134, "fp32": 2.0 ** -150, "fp64": 0.0}[prec]
+    check_backward_error(A_in, from_cm(T), piv, u, (n + 511) // 512 + 8, 2.0 ** -53 if prec == "fp64" else U32, eta_sub)
+
+
 def subnormal_matrix(kind, n, seed):
     """Every entry an FP16 subnormal or zero (|a| < 2^-14).  "gaussian":
     independent entries (partial pivoting interchanges rows).  "banded": A =
