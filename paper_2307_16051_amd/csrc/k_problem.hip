@@ -746,6 +746,7 @@ __global__ __launch_bounds__(256) void k_b_jac(const BDesc *__restrict__ d,
         if (item == off[s] && threadIdx.x == 0) {
             q.flags[FLAG_FAIL] = 0;
             q.flags[FLAG_NONFINITE] = 0;
+            q.flags[FLAG_TIMEOUT] = 0;
         }
         heq_jac_column<T>(item - off[s], q.n, q.Np, q.c, q.D, q.h, q.J, q.n, (T *)q.A, q.Np,
                           q.colscale, tl, nullptr, sh);
@@ -779,6 +780,7 @@ __global__ __launch_bounds__(256) void k_b_ir_init(const BDesc *__restrict__ d,
         q.b[i] = v;
         q.r[i] = v;
         q.u[i] = 0.0f;
+        ((uint64_t *)q.LT)[i] = 0;  // the solves' published words
     }
     __syncthreads();
     const double nb = block_nrm2(q.Np, q.b, sh);
@@ -795,14 +797,25 @@ __global__ __launch_bounds__(256) void k_b_ir_init(const BDesc *__restrict__ d,
 // One IR sweep's bookkeeping: ||r||, growth test, success test, sweep cap.
 // On growth the previous iterate is restored (Section 3.1).
 __global__ __launch_bounds__(256) void k_b_ir_check(const BDesc *__restrict__ d,
-                                                    BState *__restrict__ st, int nslots, BParams p)
+                                                    BState *__restrict__ st, int nslots, BParams p,
+                                                    int *__restrict__ tickets)
 {
     __shared__ double sh[256];
     __shared__ int grew;
     const int s = blockIdx.x;
+    if (s == 0 && threadIdx.x < B_TICKETS) tickets[threadIdx.x] = 0;  // for the next sweep
     if (s >= nslots || st[s].phase != BP_RUN || !st[s].factor || !st[s].ir_on) return;
     const BDesc &q = d[s];
     const double rnew = block_nrm2(q.Np, q.r, sh);
+    if (ld_flag(&q.flags[FLAG_TIMEOUT])) {  // a bounded wait of the solves expired
+        if (threadIdx.x == 0) {
+            st[s].phase = BP_DONE;
+            st[s].status = N3P_E_TIMEOUT;
+            st[s].factor = 0;
+            st[s].ir_on = 0;
+        }
+        return;
+    }
     if (threadIdx.x == 0) {
         BState &z = st[s];
         z.sweeps += 1;
@@ -1107,9 +1120,10 @@ hipError_t launch_b_ir_init(const BDesc *d, BState *st, int nslots, BParams p, h
     hipLaunchKernelGGL(k_b_ir_init, dim3(nslots), dim3(256), 0, s, d, st, nslots, p);
     return hipGetLastError();
 }
-hipError_t launch_b_ir_check(const BDesc *d, BState *st, int nslots, BParams p, hipStream_t s)
+hipError_t launch_b_ir_check(const BDesc *d, BState *st, int nslots, BParams p, int *tickets,
+                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_b_ir_check, dim3(nslots), dim3(256), 0, s, d, st, nslots, p);
+    hipLaunchKernelGGL(k_b_ir_check, dim3(nslots), dim3(256), 0, s, d, st, nslots, p, tickets);
     return hipGetLastError();
 }
 hipError_t launch_b_ir_final(const BDesc *d, BState *st, int nslots, BParams p, hipStream_t s)

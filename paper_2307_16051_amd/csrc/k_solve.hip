@@ -367,36 +367,37 @@ __device__ __forceinline__ void load_row(V (&r)[BS], const V *__restrict__ R, in
     for (int c = 0; c < BS; ++c) r[c] = R[lane * (BS + 1) + c];
 }
 
-// ---------------------------------------------------------------- lower
+// ------------------------------------------------------- one row block
 // round_out (both solves): every solution entry is rounded to the factor
 // type T as it is formed, before later blocks use it -- the solve held in
 // the low precision for the scaled correction of eq. (2.19) (Section 2.3).
 //
-// y = L^{-1} (P b): L unit lower (below the diagonal of LU), perm[i] = the
-// original row placed at position i (null = identity).  Block `blk` owns rows
-// [blk*BS, blk*BS + BS) (lane = row); wavefront w consumes tiles w, w+4, ...
-// below blk - 1, keeping the next tile's loads in flight while it consumes
-// the current one.  Tile blk - 1 enters through Mx = D^{-1} L_{b,b-1}.
-template <typename T, typename V, int BS>
-__global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restrict__ LU, int64_t lda,
-                                                    const int32_t *__restrict__ perm,
-                                                    const V *__restrict__ b, V *__restrict__ y,
-                                                    int *__restrict__ sync, uint32_t epoch,
-                                                    int *__restrict__ flags, int round_out)
+// Block `blk` owns rows [blk*BS, blk*BS + BS) (lane = row).  rhs(row) is the
+// right-hand side of a row, out(row, w) takes its solution; both are called
+// by wavefront 0 for rows < n.
+template <typename V, int BS> struct TrsvLds {
+    static constexpr int LS = lds_stride<BS>::LS;
+    V Dr[BS * LS];  // D, then Mx
+    V Eb[BS * LS];  // L_{b,b-1} or U_{b,b+1}
+    V Di[BS * LS];  // D^{-1}
+    V rd[BS];
+    V part[4][BS];
+    __attribute__((aligned(16))) V vb[4][BS];  // each wavefront's broadcast vector
+};
+
+// Lower: wavefront w consumes tiles w, w+4, ... below blk - 1, keeping the
+// next tile's loads in flight while it consumes the current one.  Tile
+// blk - 1 enters through Mx = D^{-1} L_{b,b-1}.
+template <typename T, typename V, int BS, typename Rhs, typename Out>
+__device__ __forceinline__ void trsv_lower_block(TrsvLds<V, BS> &sh, int blk, int64_t n,
+                                                 const T *__restrict__ LU, int64_t lda,
+                                                 uint64_t *tags, uint32_t epoch,
+                                                 int *__restrict__ flags, int round_out, Rhs rhs,
+                                                 Out out)
 {
     static_assert(BS == 64, "a wavefront spans one tile");
-    constexpr int LS = lds_stride<BS>::LS, PT = BS / 4;
-    __shared__ int s_blk;
-    __shared__ V Dr[BS * LS];     // D, then Mx
-    __shared__ V Eb[BS * LS];     // L_{b,b-1}
-    __shared__ V Di[BS * LS];     // D^{-1}
-    __shared__ V part[4][BS];
-    __shared__ __attribute__((aligned(16))) V vb[4][BS];  // each wavefront's broadcast vector
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    if (tid == 0) s_blk = take_ticket(sync, epoch, gridDim.x);
-    __syncthreads();
-    const int blk = s_blk;
-    uint64_t *tags = tag_words(sync);
+    constexpr int LS = TrsvLds<V, BS>::LS, PT = BS / 4;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t r0 = (int64_t)blk * BS;
     const int64_t row = r0 + lane;
     const bool rv = row < n;
@@ -420,12 +421,12 @@ __global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restri
 #pragma unroll
         for (int k = 0; k < PT; ++k) {
             const int j = wv + 4 * k;
-            Dr[lane * LS + j] = j < lane && rv ? (V)to_f32(d[k]) : (V)0;
-            Di[lane * LS + j] = 0;
-            if (blk > 0) Eb[lane * LS + j] = rv ? (V)to_f32(e[k]) : (V)0;
+            sh.Dr[lane * LS + j] = j < lane && rv ? (V)to_f32(d[k]) : (V)0;
+            sh.Di[lane * LS + j] = 0;
+            if (blk > 0) sh.Eb[lane * LS + j] = rv ? (V)to_f32(e[k]) : (V)0;
         }
     }
-    diag_inverse_mx<V, BS, true>(Dr, nullptr, Eb, Di, blk > 0, lane, wv);
+    diag_inverse_mx<V, BS, true>(sh.Dr, nullptr, sh.Eb, sh.Di, blk > 0, lane, wv);
     int jb = wv;
     if (jb < last) {
         load_tile_row<T, V, BS>(fv, LU, lda, rowc, (int64_t)jb * BS, n);
@@ -438,66 +439,48 @@ __global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restri
             nxt.issue(tags, (int64_t)nj * BS + lane, true);
         }
         cur.settle(tags, (int64_t)jb * BS + lane, true, epoch, &spins, flags, std::min(32, last - jb - 2));
-        acc += row_times_lds<V, BS>(fv, cur.value(), vb[wv], lane);
+        acc += row_times_lds<V, BS>(fv, cur.value(), sh.vb[wv], lane);
 #pragma unroll
         for (int c = 0; c < BS; ++c) fv[c] = fvn[c];
         cur = nxt;
     }
-    part[wv][lane] = acc;
+    sh.part[wv][lane] = acc;
     __syncthreads();
     if (wv == 0) {
         V z = 0;
-        if (rv) {
-            const int64_t src = perm ? (int64_t)perm[row] : row;
-            z = b[src] - ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
-        }
+        if (rv) z = rhs(row) - ((sh.part[0][lane] + sh.part[1][lane]) + (sh.part[2][lane] + sh.part[3][lane]));
         V rr[BS];
-        load_row<V, BS>(rr, Di, lane);
-        V w = row_times_lds<V, BS>(rr, z, vb[0], lane);
+        load_row<V, BS>(rr, sh.Di, lane);
+        V w = row_times_lds<V, BS>(rr, z, sh.vb[0], lane);
         if (blk > 0) {
             // the only work left after the predecessor publishes: one product
             // with a row already in registers
-            load_row<V, BS>(rr, Dr, lane);
+            load_row<V, BS>(rr, sh.Dr, lane);
             lane_word<V> xp;
             xp.issue(tags, (int64_t)last * BS + lane, true);
             xp.template settle_ring<8>(tags, (int64_t)last * BS + lane, true, epoch, &spins, flags);
-            w -= row_times_lds<V, BS>(rr, xp.value(), vb[0], lane);
+            w -= row_times_lds<V, BS>(rr, xp.value(), sh.vb[0], lane);
         }
         if (round_out) w = (V)to_f32((T)w);  // solution held in the factor precision
         if (rv) {
-            y[row] = w;
             tagged<V>::put(tags, row, w, epoch);
+            out(row, w);
         }
     }
 }
 
-// ---------------------------------------------------------------- upper
-// x = S U^{-1} y with S = diag(colscale) (null = identity).  Blocks run from
-// the last to the first; other blocks read the unscaled solution (tagged).
-// Tile blk + 1 enters through Mx = D^{-1} U_{b,b+1}.
-template <typename T, typename V, int BS>
-__global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restrict__ LU, int64_t lda,
-                                                    const V *__restrict__ yin,
-                                                    const float *__restrict__ colscale,
-                                                    V *__restrict__ x, int *__restrict__ sync,
-                                                    uint32_t epoch, int *__restrict__ flags,
-                                                    int round_out)
+// Upper: blocks run from the last (nb - 1) to the first; tile blk + 1 enters
+// through Mx = D^{-1} U_{b,b+1}.
+template <typename T, typename V, int BS, typename Rhs, typename Out>
+__device__ __forceinline__ void trsv_upper_block(TrsvLds<V, BS> &sh, int blk, int nb, int64_t n,
+                                                 const T *__restrict__ LU, int64_t lda,
+                                                 uint64_t *tags, uint32_t epoch,
+                                                 int *__restrict__ flags, int round_out, Rhs rhs,
+                                                 Out out)
 {
     static_assert(BS == 64, "a wavefront spans one tile");
-    constexpr int LS = lds_stride<BS>::LS, PT = BS / 4;
-    __shared__ int s_blk;
-    __shared__ V Dr[BS * LS];     // D, then Mx
-    __shared__ V Eb[BS * LS];     // U_{b,b+1}
-    __shared__ V Di[BS * LS];     // D^{-1}
-    __shared__ V rd[BS];
-    __shared__ V part[4][BS];
-    __shared__ __attribute__((aligned(16))) V vb[4][BS];  // each wavefront's broadcast vector
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nb = (int)((n + BS - 1) / BS);
-    if (tid == 0) s_blk = nb - 1 - take_ticket(sync, epoch, gridDim.x);
-    __syncthreads();
-    const int blk = s_blk;
-    uint64_t *tags = tag_words(sync);
+    constexpr int LS = TrsvLds<V, BS>::LS, PT = BS / 4;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t r0 = (int64_t)blk * BS;
     const int64_t row = r0 + lane;
     const bool rv = row < n;
@@ -523,13 +506,13 @@ __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restri
             const int j = wv + 4 * k;
             const bool in = rv && r0 + j < n;
             const V u = in ? (V)to_f32(d[k]) : (V)0;
-            Dr[lane * LS + j] = j > lane ? u : (V)0;
-            if (j == lane) rd[j] = in ? (V)1 / u : (V)1;
-            Di[lane * LS + j] = 0;
-            if (has_next) Eb[lane * LS + j] = rv && r0 + BS + j < n ? (V)to_f32(e[k]) : (V)0;
+            sh.Dr[lane * LS + j] = j > lane ? u : (V)0;
+            if (j == lane) sh.rd[j] = in ? (V)1 / u : (V)1;
+            sh.Di[lane * LS + j] = 0;
+            if (has_next) sh.Eb[lane * LS + j] = rv && r0 + BS + j < n ? (V)to_f32(e[k]) : (V)0;
         }
     }
-    diag_inverse_mx<V, BS, false>(Dr, rd, Eb, Di, has_next, lane, wv);
+    diag_inverse_mx<V, BS, false>(sh.Dr, sh.rd, sh.Eb, sh.Di, has_next, lane, wv);
     int jb = nb - 1 - wv;
     if (jb > next) {
         load_tile_row<T, V, BS>(fv, LU, lda, rowc, (int64_t)jb * BS, n);
@@ -543,32 +526,73 @@ __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restri
         }
         const bool valid = (int64_t)jb * BS + lane < n;
         cur.settle(tags, (int64_t)jb * BS + lane, valid, epoch, &spins, flags, std::min(32, jb - next - 2));
-        acc += row_times_lds<V, BS>(fv, valid ? cur.value() : (V)0, vb[wv], lane);
+        acc += row_times_lds<V, BS>(fv, valid ? cur.value() : (V)0, sh.vb[wv], lane);
 #pragma unroll
         for (int c = 0; c < BS; ++c) fv[c] = fvn[c];
         cur = nxt;
     }
-    part[wv][lane] = acc;
+    sh.part[wv][lane] = acc;
     __syncthreads();
     if (wv == 0) {
-        const V z = rv ? yin[row] - ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane])) : (V)0;
+        const V z = rv ? rhs(row) - ((sh.part[0][lane] + sh.part[1][lane]) + (sh.part[2][lane] + sh.part[3][lane])) : (V)0;
         V rr[BS];
-        load_row<V, BS>(rr, Di, lane);
-        V w = row_times_lds<V, BS>(rr, z, vb[0], lane);
+        load_row<V, BS>(rr, sh.Di, lane);
+        V w = row_times_lds<V, BS>(rr, z, sh.vb[0], lane);
         if (has_next) {
-            load_row<V, BS>(rr, Dr, lane);
+            load_row<V, BS>(rr, sh.Dr, lane);
             const bool valid = (int64_t)next * BS + lane < n;
             lane_word<V> xn;
             xn.issue(tags, (int64_t)next * BS + lane, valid);
             xn.template settle_ring<8>(tags, (int64_t)next * BS + lane, valid, epoch, &spins, flags);
-            w -= row_times_lds<V, BS>(rr, valid ? xn.value() : (V)0, vb[0], lane);
+            w -= row_times_lds<V, BS>(rr, valid ? xn.value() : (V)0, sh.vb[0], lane);
         }
         if (round_out) w = (V)to_f32((T)w);
         if (rv) {
             tagged<V>::put(tags, row, w, epoch);
-            x[row] = colscale ? w * (V)colscale[row] : w;
+            out(row, w);
         }
     }
+}
+
+// ------------------------------------------------------------ single solves
+// y = L^{-1} (P b): L unit lower (below the diagonal of LU), perm[i] = the
+// original row placed at position i (null = identity).
+template <typename T, typename V, int BS>
+__global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restrict__ LU, int64_t lda,
+                                                    const int32_t *__restrict__ perm,
+                                                    const V *__restrict__ b, V *__restrict__ y,
+                                                    int *__restrict__ sync, uint32_t epoch,
+                                                    int *__restrict__ flags, int round_out)
+{
+    __shared__ int s_blk;
+    __shared__ TrsvLds<V, BS> sh;
+    if (threadIdx.x == 0) s_blk = take_ticket(sync, epoch, gridDim.x);
+    __syncthreads();
+    trsv_lower_block<T, V, BS>(
+        sh, s_blk, n, LU, lda, tag_words(sync), epoch, flags, round_out,
+        [&](int64_t row) { return b[perm ? (int64_t)perm[row] : row]; },
+        [&](int64_t row, V w) { y[row] = w; });
+}
+
+// x = S U^{-1} y with S = diag(colscale) (null = identity); other blocks read
+// the unscaled solution (tagged).
+template <typename T, typename V, int BS>
+__global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restrict__ LU, int64_t lda,
+                                                    const V *__restrict__ yin,
+                                                    const float *__restrict__ colscale,
+                                                    V *__restrict__ x, int *__restrict__ sync,
+                                                    uint32_t epoch, int *__restrict__ flags,
+                                                    int round_out)
+{
+    __shared__ int s_blk;
+    __shared__ TrsvLds<V, BS> sh;
+    const int nb = (int)((n + BS - 1) / BS);
+    if (threadIdx.x == 0) s_blk = nb - 1 - take_ticket(sync, epoch, gridDim.x);
+    __syncthreads();
+    trsv_upper_block<T, V, BS>(
+        sh, s_blk, nb, n, LU, lda, tag_words(sync), epoch, flags, round_out,
+        [&](int64_t row) { return yin[row]; },
+        [&](int64_t row, V w) { x[row] = colscale ? w * (V)colscale[row] : w; });
 }
 
 // ticket (4 ints, keeps the tag words 16-byte aligned) + 2 tag words per entry
@@ -941,111 +965,84 @@ hipError_t launch_krylov_update(int64_t n, const float *V, int64_t ldv, int k, c
 
 
 // ====================================================== batched engine kernels
-// One workgroup per slot (N <= B_MAX_NP): y = L^{-1} r (unit lower), then
-// z = U^{-1} y, d = S z (S the FP16 column scale), and uprev = u, u += d:
-// the correction step of the IR algorithm of Section 2.2 with the stored half-precision factors
-// promoted to FP32 as they are read (Section 2.3).  Blocked by 64: one wave
-// substitutes the diagonal block (a row per lane, readlane broadcasts), then
-// all waves update the remaining rows with coalesced column reads while the
-// next diagonal block's loads are in flight.
-template <typename T>
-__global__ __launch_bounds__(B_SOLVE_THREADS) void k_b_solve(const BDesc *__restrict__ d,
-                                                             const BState *__restrict__ st,
-                                                             int nslots)
+// The correction step of the IR algorithm of Section 2.2 for every refining
+// slot: y = L^{-1} r, then z = U^{-1} y, d = S z (S the FP16 column scale),
+// uprev = u, u += d, with the stored half-precision factors promoted to FP32
+// as they are read (Section 2.3); LOWER, then upper, one launch each.
+//
+// The row blocks are those of the single solves.  A fixed grid takes them by
+// ticket, all slots' first blocks, then all second ones, and so on: a block
+// waits only on blocks of its own slot with smaller tickets, which running
+// workgroups hold, so the waits end whatever the grid.  The published words
+// and y lie in the slot's LT, which only the factorisation uses; k_b_ir_init
+// clears the words each Newton step and the tags count the sweeps, so no tag
+// repeats.  The tickets are cleared by the sweep's k_b_ir_check.
+// With one workgroup per slot the 32 blocks of N = 2048 passed through one
+// CU: 347 us a call for 32 requests of 128 to 2048 rows, now 101 for the two
+// launches (240 for one workgroup with the substitution of a block beside the
+// update by the one before it).
+template <typename T, bool LOWER>
+__global__ __launch_bounds__(256) void k_b_trsv(const BDesc *__restrict__ d,
+                                                const BState *__restrict__ st, int nslots,
+                                                int *__restrict__ ticket)
 {
-    constexpr int NT = B_SOLVE_THREADS;
-    __shared__ float y[B_MAX_NP];
-    __shared__ float Dg[64][65];
-    const int s = blockIdx.x;
-    if (s >= nslots || st[s].phase != BP_RUN || !st[s].factor || !st[s].ir_on) return;
-    const BDesc &q = d[s];
-    const int64_t Np = q.Np, n = q.n;
-    const T *__restrict__ A = (const T *)q.A;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int nb = (int)(Np / 64);
-    // the next diagonal block is fetched into registers while the current
-    // block's update runs, and stored to Dg once the substitution is done
-    static_assert(NT * 4 == 64 * 64, "four diagonal entries per thread");
-    float pre[4];
-    auto fetch = [&](int64_t b0) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int e = t + r * NT, i = e & 63, k = e >> 6;
-            pre[r] = to_f32(A[(b0 + i) + (b0 + k) * Np]);
-        }
-    };
-    auto put = [&]() {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int e = t + r * NT, i = e & 63, k = e >> 6;
-            Dg[i][k] = pre[r];
-        }
-    };
-    for (int64_t i = t; i < Np; i += NT) y[i] = q.r[i];
-    fetch(0);
-    put();
-    __syncthreads();
-    for (int blk = 0; blk < nb; ++blk) {  // forward, unit lower
-        const int64_t b0 = (int64_t)blk * 64;
-        if (wave == 0) {
-            float lr[64];
-#pragma unroll
-            for (int k = 0; k < 64; ++k) lr[k] = lane > k ? Dg[lane][k] : 0.0f;
-            float yi = y[b0 + lane];
-#pragma unroll
-            for (int k = 0; k < 64; ++k) yi -= lr[k] * lane_bcast(yi, k);
-            y[b0 + lane] = yi;
-        }
-        __syncthreads();
-        const bool more = blk + 1 < nb;
-        if (more) fetch(b0 + 64);
-        for (int64_t i = b0 + 64 + t; i < Np; i += NT) {
-            const T *__restrict__ col = A + i + b0 * Np;
-            float acc = y[i];
-#pragma unroll 16
-            for (int k = 0; k < 64; ++k) acc -= to_f32(col[(int64_t)k * Np]) * y[b0 + k];
-            y[i] = acc;
-        }
-        if (more) put();
-        __syncthreads();
+    constexpr int BS = 64, NLEV = B_MAX_NP / BS;
+    static_assert(B_MAX_SLOTS <= 256 && NLEV <= 256, "one thread per slot and per level");
+    __shared__ TrsvLds<float, BS> sh;
+    __shared__ int nbs[B_MAX_SLOTS], order[B_MAX_SLOTS], lev[NLEV + 1], s_item;
+    const int t = threadIdx.x;
+    // blocks per slot, the slots by falling number of blocks, and the number
+    // of items on the levels before each
+    int nb = 0;
+    if (t < nslots) {
+        if (st[t].phase == BP_RUN && st[t].factor && st[t].ir_on) nb = (int)(d[t].Np / BS);
+        nbs[t] = nb;
     }
-    fetch((int64_t)(nb - 1) * 64);
-    put();
     __syncthreads();
-    for (int blk = nb - 1; blk >= 0; --blk) {  // backward, upper
-        const int64_t b0 = (int64_t)blk * 64;
-        if (wave == 0) {
-            float ur[64];
-#pragma unroll
-            for (int k = 0; k < 64; ++k) ur[k] = lane < k ? Dg[lane][k] : 0.0f;
-            const float rd = 1.0f / Dg[lane][lane];
-            float yi = y[b0 + lane];
-#pragma unroll
-            for (int k = 63; k >= 0; --k) {
-                if (lane == k) yi *= rd;
-                yi -= ur[k] * lane_bcast(yi, k);
-            }
-            y[b0 + lane] = yi;
-        }
-        __syncthreads();
-        const bool more = blk > 0;
-        if (more) fetch(b0 - 64);
-        for (int64_t i = t; i < b0; i += NT) {
-            const T *__restrict__ col = A + i + b0 * Np;
-            float acc = y[i];
-#pragma unroll 16
-            for (int k = 0; k < 64; ++k) acc -= to_f32(col[(int64_t)k * Np]) * y[b0 + k];
-            y[i] = acc;
-        }
-        if (more) put();
-        __syncthreads();
+    int rank = 0, cnt = 0;
+    for (int j = 0; j < nslots; ++j) {
+        const int o = nbs[j];
+        rank += o > nb || (o == nb && j < t);
+        cnt += o > t;
     }
-    for (int64_t i = t; i < Np; i += NT) {
-        float di = 0.0f;
-        if (i < n) di = q.colscale ? y[i] * q.colscale[i] : y[i];
-        const float ui = q.u[i];
-        q.uprev[i] = ui;
-        q.u[i] = ui + di;
+    if (t < nslots) order[rank] = t;
+    if (t < NLEV) lev[t + 1] = cnt;
+    __syncthreads();
+    if (t == 0) {
+        lev[0] = 0;
+        for (int l = 0; l < NLEV; ++l) lev[l + 1] += lev[l];
+    }
+    __syncthreads();
+    const int total = lev[NLEV];
+    for (;;) {
+        if (t == 0) s_item = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const int item = s_item;
+        if (item >= total) return;
+        const int l = b_find(lev, NLEV, item);
+        const int s = order[item - lev[l]];
+        const BDesc &q = d[s];
+        const int64_t Np = q.Np, n = q.n;
+        uint64_t *tags = (uint64_t *)q.LT;
+        float *y = (float *)(tags + Np);
+        const uint32_t tag = 2 * (uint32_t)st[s].sweeps + (LOWER ? 1 : 2);
+        if constexpr (LOWER) {
+            trsv_lower_block<T, float, BS>(
+                sh, l, Np, (const T *)q.A, Np, tags, tag, q.flags, 0,
+                [&](int64_t row) { return q.r[row]; }, [&](int64_t row, float w) { y[row] = w; });
+        } else {
+            const int nblk = (int)(Np / BS);
+            trsv_upper_block<T, float, BS>(
+                sh, nblk - 1 - l, nblk, Np, (const T *)q.A, Np, tags, tag, q.flags, 0,
+                [&](int64_t row) { return y[row]; },
+                [&](int64_t row, float w) {
+                    const float di = row < n ? (q.colscale ? w * q.colscale[row] : w) : 0.0f;
+                    const float ui = q.u[row];
+                    q.uprev[row] = ui;
+                    q.u[row] = ui + di;
+                });
+        }
+        __syncthreads();
     }
 }
 
@@ -1076,14 +1073,24 @@ __global__ __launch_bounds__(MV_NT) void k_b_gemv(const BDesc *__restrict__ d,
     }
 }
 
-hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots, hipStream_t s)
+// two workgroups fit a CU (256 registers a lane, 53 KB of LDS)
+constexpr unsigned B_TRSV_GRID = 512;
+template <typename T>
+static hipError_t b_solve_t(const BDesc *d, const BState *st, int nslots, int *tickets, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_b_trsv<T, true>), dim3(B_TRSV_GRID), dim3(256), 0, s, d, st, nslots, tickets);
+    hipLaunchKernelGGL((k_b_trsv<T, false>), dim3(B_TRSV_GRID), dim3(256), 0, s, d, st, nslots, tickets + 1);
+    return hipGetLastError();
+}
+
+hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots, int *tickets,
+                          hipStream_t s)
 {
     switch (prec) {
-    case N3P_FP16: hipLaunchKernelGGL(k_b_solve<f16>, dim3(nslots), dim3(B_SOLVE_THREADS), 0, s, d, st, nslots); break;
-    case N3P_BF16: hipLaunchKernelGGL(k_b_solve<bf16>, dim3(nslots), dim3(B_SOLVE_THREADS), 0, s, d, st, nslots); break;
-    default: return hipErrorInvalidValue;
+    case N3P_FP16: return b_solve_t<f16>(d, st, nslots, tickets, s);
+    case N3P_BF16: return b_solve_t<bf16>(d, st, nslots, tickets, s);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_b_gemv(const BDesc *d, const BState *st, int nslots, int grid, hipStream_t s)

@@ -96,7 +96,8 @@ size_t request_layout(int64_t n, int prec, BDesc *d, char *base)
 
 size_t fixed_bytes(int max_slots)
 {
-    return al(sizeof(BDesc) * (size_t)max_slots) + al(sizeof(BState) * (size_t)max_slots);
+    return al(sizeof(BDesc) * (size_t)max_slots) + al(sizeof(BState) * (size_t)max_slots) +
+           al(sizeof(int) * B_TICKETS);
 }
 
 // First-fit allocator over [0, size) of the pool, in 256-byte units.
@@ -160,6 +161,7 @@ struct n3p_engine {
     size_t pool_bytes = 0;
     BDesc *d_desc = nullptr;
     BState *d_state = nullptr;
+    int *d_tickets = nullptr;                   // zero between sweeps
     std::vector<BDesc> hdesc;
     std::vector<BState> hstate;
     std::vector<size_t> slot_off, slot_bytes;  // pool region per slot (0 bytes: free)
@@ -185,9 +187,9 @@ struct n3p_engine {
     }
     int seq_sweep()
     {
-        BHIP(launch_b_solve(cfg.lu_prec, d_desc, d_state, nslots(), s));
+        BHIP(launch_b_solve(cfg.lu_prec, d_desc, d_state, nslots(), d_tickets, s));
         BHIP(launch_b_gemv(d_desc, d_state, nslots(), cfg.vec_grid, s));
-        BHIP(launch_b_ir_check(d_desc, d_state, nslots(), prm, s));
+        BHIP(launch_b_ir_check(d_desc, d_state, nslots(), prm, d_tickets, s));
         return 0;
     }
     int seq_final()
@@ -407,6 +409,7 @@ N3P_API int n3p_engine_create(n3p_engine **out, const n3p_engine_config *cfg,
     e->pool_bytes = pool_bytes - lost;
     e->d_desc = (BDesc *)base;
     e->d_state = (BState *)(base + al(sizeof(BDesc) * (size_t)c.max_slots));
+    e->d_tickets = (int *)((char *)e->d_state + al(sizeof(BState) * (size_t)c.max_slots));
     e->req_base = fixed;
     e->alloc.init(e->pool_bytes - fixed);
     e->hdesc.assign(c.max_slots, BDesc{});
@@ -433,6 +436,7 @@ N3P_API int n3p_engine_create(n3p_engine **out, const n3p_engine_config *cfg,
                        hipMemcpyHostToDevice, e->s) != hipSuccess ||
         hipMemcpyAsync(e->d_state, e->hstate.data(), sizeof(BState) * c.max_slots,
                        hipMemcpyHostToDevice, e->s) != hipSuccess ||
+        launch_fill_i32(e->d_tickets, 0, B_TICKETS, e->s) != hipSuccess ||
         hipStreamSynchronize(e->s) != hipSuccess)
         st = N3P_E_HIP;
     if (st) {
