@@ -269,124 +269,87 @@ __device__ __forceinline__ float block_max(float v, float *red)
     return m;
 }
 
-// max over a block of NW wavefronts of two values at once
-template <int NW>
-__device__ __forceinline__ float2 block_max2(float2 v, float2 *red)
-{
-    v.x = wave_max(v.x);
-    v.y = wave_max(v.y);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float2 m = red[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) {
-        m.x = fmaxf(m.x, red[i].x);
-        m.y = fmaxf(m.y, red[i].y);
-    }
-    __syncthreads();
-    return m;
-}
-
 typedef float DmRow[PT + 1];
 
-// Inverses of the eight diagonal 8x8 blocks of U and of L, in place: wave J,
-// lanes 0..7 the columns of U_JJ^{-1} (back substitution), lanes 8..15 those
-// of L_JJ^{-1} (forward substitution, unit diagonal).  The block's entries
-// are read into registers first, so the reads issue together instead of one
-// per step of the dependent chain.
-__device__ __forceinline__ void inv_diag8(DmRow *Dm, int J, int lane)
+// Triangular inverses in place in Dm: U^{-1} on and above the diagonal,
+// L^{-1} (unit diagonal, not stored) below it.  Waves 0..3 take U, waves
+// 4..7 L: the four diagonal 16x16 blocks by substitution, one per wave, then
+// 16 -> 32 -> 64: for a pair of inverted diagonal blocks X11, X22 and the
+// block U12 (L21) between them, X12 = -X11 (U12 X22), X21 = -X22 (L21 X11)
+// on v_mfma_f32_16x16x4f32, the inner product staying in the registers it was
+// formed in.  This is on the chain of leaves: 2.1 us a leaf at @INV@ against
+// 6.0 us for 8x8 blocks, a doubling on the VALU and two that passed the inner
+// products through LDS.  Each step returns the largest magnitude this lane
+// wrote.
+
+// Element (i, m) of the triangle's inverse, its zeros and unit diagonal filled in.
+__device__ __forceinline__ float tri_at(const DmRow *Dm, int tri, int i, int m)
 {
-    const int c = lane & 7, b = 8 * J;
-    float xd[8];
-    if (lane < 8) {
-        float u[8][8];
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr)
-#pragma unroll
-            for (int m = rr; m < 8; ++m) u[rr][m] = Dm[b + rr][b + m];
-#pragma unroll
-        for (int rr = 7; rr >= 0; --rr) {
-            float v = rr == c ? 1.0f : 0.0f;
-#pragma unroll
-            for (int m = rr + 1; m < 8; ++m) v -= u[rr][m] * xd[m];
-            xd[rr] = v * rcp_nr(u[rr][rr]);
-        }
-    } else if (lane < 16) {
-        float l[8][8];
-#pragma unroll
-        for (int rr = 1; rr < 8; ++rr)
-#pragma unroll
-            for (int m = 0; m < rr; ++m) l[rr][m] = Dm[b + rr][b + m];
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr) {
-            float v = rr == c ? 1.0f : 0.0f;
-#pragma unroll
-            for (int m = 0; m < rr; ++m) v -= l[rr][m] * xd[m];
-            xd[rr] = v;
-        }
-    }
-    __syncthreads();
-    if (lane < 8) {
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr)
-            if (rr <= c) Dm[b + rr][b + c] = xd[rr];
-    } else if (lane < 16) {
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr)
-            if (rr > c) Dm[b + rr][b + c] = xd[rr];
-    }
+    const float x = Dm[i][m];
+    return tri == 0 ? (m >= i ? x : 0.0f) : (m < i ? x : (m == i ? 1.0f : 0.0f));
 }
 
-// Doubling 8 -> 16 on the VALU: pairs p = 0, 16, 32, 48; thread t takes
-// entry (i, c) of pair q of the U (t < 256) or L (t >= 256) triangle.
-__device__ __forceinline__ void inv_double8(DmRow *Dm, float *Ts, int t)
+// The 16x16 diagonal blocks, by substitution: wave 4 tri + q block q.  The
+// four lanes 4 c + g of a quad share column c: lane g keeps the entries of
+// rows 4 j + g and sums their part of each row's product, and the quad adds
+// up (with one lane per column, a quarter of the lanes, the 120 products and
+// their operands took 2 us).  A wave reads and writes its own triangle only.
+__device__ __forceinline__ float inv_diag16(DmRow *Dm, int w, int lane)
 {
-    const int tri = t >> 8, q = (t >> 6) & 3, i = (t >> 3) & 7, c = t & 7, p = 16 * q;
-    // each phase reads its 16 operands first, then sums in order
-    float ra[8], rb[8];
-    float v = 0.0f;
-    if (tri == 0) {  // T = U12 X22 (X22 upper)
+    const int b = 16 * (w & 3), c = lane >> 2, g = lane & 3;
+    float xg[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mx = 0.0f;
+    auto quad_sum = [](float v) {
+        v += dpp_f(v, 0);
+        return v + dpp_f(v, 1);
+    };
+    if (w < 4) {
+        float rd[4];
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            rb[m] = Dm[p + 8 + m][p + 8 + c];
-            ra[m] = Dm[p + i][p + 8 + m];
+        for (int j = 0; j < 4; ++j) rd[j] = rcp_nr(Dm[b + 4 * j + g][b + 4 * j + g]);
+#pragma unroll
+        for (int r = 15; r >= 0; --r) {
+            const int j0 = r >> 2;
+            float s = 0.0f;
+#pragma unroll
+            for (int j = 3; j > j0; --j) s += Dm[b + r][b + 4 * j + g] * xg[j];
+            const float ub = Dm[b + r][b + 4 * j0 + g];
+            s += (g > (r & 3) ? ub : 0.0f) * xg[j0];
+            float rr;
+            switch (r & 3) {
+            case 0: rr = quad_bcast<0>(rd[j0]); break;
+            case 1: rr = quad_bcast<1>(rd[j0]); break;
+            case 2: rr = quad_bcast<2>(rd[j0]); break;
+            default: rr = quad_bcast<3>(rd[j0]); break;
+            }
+            const float x = ((r == c ? 1.0f : 0.0f) - quad_sum(s)) * rr;
+            xg[j0] = g == (r & 3) ? x : xg[j0];
         }
 #pragma unroll
-        for (int m = 0; m < 8; ++m) v += ra[m] * (m <= c ? rb[m] : 0.0f);
-    } else {         // T = L21 X11 (X11 unit lower)
+        for (int j = 0; j < 4; ++j)
+            if (4 * j + g <= c) {
+                Dm[b + 4 * j + g][b + c] = xg[j];
+                mx = fmaxf(mx, fabsf(xg[j]));
+            }
+    } else {
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            rb[m] = Dm[p + m][p + c];
-            ra[m] = Dm[p + 8 + i][p + m];
+        for (int r = 0; r < 16; ++r) {
+            const int j0 = r >> 2;
+            float s = 0.0f;
+#pragma unroll
+            for (int j = 0; j < j0; ++j) s += Dm[b + r][b + 4 * j + g] * xg[j];
+            const float lb = Dm[b + r][b + 4 * j0 + g];
+            s += (g < (r & 3) ? lb : 0.0f) * xg[j0];
+            const float x = (r == c ? 1.0f : 0.0f) - quad_sum(s);
+            xg[j0] = g == (r & 3) ? x : xg[j0];
         }
 #pragma unroll
-        for (int m = 0; m < 8; ++m) v += ra[m] * (m > c ? rb[m] : (m == c ? 1.0f : 0.0f));
+        for (int j = 0; j < 4; ++j)
+            if (4 * j + g > c) {
+                Dm[b + 4 * j + g][b + c] = xg[j];
+                mx = fmaxf(mx, fabsf(xg[j]));
+            }
     }
-    Ts[t] = v;
-    __syncthreads();
-    const float *T = Ts + (t & ~63);  // this pair's T, row-major 8x8
-    v = 0.0f;
-    if (tri == 0) {  // X12 = -X11 T (X11 upper)
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            ra[m] = Dm[p + i][p + m];
-            rb[m] = T[m * 8 + c];
-        }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) v += (m >= i ? ra[m] : 0.0f) * rb[m];
-    } else {         // X21 = -X22 T (X22 unit lower)
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            ra[m] = Dm[p + 8 + i][p + 8 + m];
-            rb[m] = T[m * 8 + c];
-        }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) v += (m < i ? ra[m] : (m == i ? 1.0f : 0.0f)) * rb[m];
-    }
-    __syncthreads();
-    if (tri == 0) Dm[p + i][p + 8 + c] = -v;
-    else Dm[p + 8 + i][p + c] = -v;
-    __syncthreads();
+    return mx;
 }
 
 // 16x16 tile of A B (K = k_len, a multiple of 4) on the FP32 matrix cores
@@ -412,71 +375,54 @@ __device__ __forceinline__ f32x4 mm16f32(FA fa, FB fb, int lane)
     return acc;
 }
 
-// Doubling BS -> 2 BS (BS = 16 or 32) on the matrix cores.  Work items:
-// (triangle, pair, 16x16 output tile); BS = 16: 2 pairs x 1 tile per
-// triangle, BS = 32: 1 pair x 4 tiles per triangle -- four items per
-// triangle, one per wave (waves 0..3 U, 4..7 L).
-template <int BS>
-__device__ __forceinline__ void inv_double_mfma(DmRow *Dm, float *Ts, int w, int lane)
+// acc - P T, T a 16x16 fragment as mm16f32 left it: register q of lane l
+// holds row 4 (l >> 4) + q of T, so step q takes that column of P
+template <typename FP>
+__device__ __forceinline__ f32x4 mm16_sub(f32x4 acc, FP fp, const f32x4 &t, int lane)
 {
-    constexpr int NT = BS / 16;                 // output tiles per side
-    constexpr int NPAIR = PT / (2 * BS);        // pairs per triangle
-    const int tri = w >> 2, item = w & 3;
-    const int q = item / (NT * NT), ti = (item / NT) % NT, tc = item % NT;
-    const bool on = q < NPAIR;                  // BS = 16: items 2, 3 have no pair
-    const int p = 2 * BS * (on ? q : 0);
-    float *T = Ts + tri * 1024 + (on ? q : 0) * BS * BS;   // row-major BS x BS
     const int ci = lane & 15, kq = lane >> 4;
-    f32x4 acc;
-    if (!on) {
-    } else if (tri == 0) {  // T = U12 X22, X22 upper
-        acc = mm16f32<BS>([&](int i, int m) { return Dm[p + 16 * ti + i][p + BS + m]; },
-                          [&](int m, int c) {
-                              const int cc = 16 * tc + c;
-                              const float x = Dm[p + BS + m][p + BS + cc];
-                              return m <= cc ? x : 0.0f;
-                          },
-                          lane);
-    } else {         // T = L21 X11, X11 unit lower
-        acc = mm16f32<BS>([&](int i, int m) { return Dm[p + BS + 16 * ti + i][p + m]; },
-                          [&](int m, int c) {
-                              const int cc = 16 * tc + c;
-                              const float x = Dm[p + m][p + cc];
-                              return m > cc ? x : (m == cc ? 1.0f : 0.0f);
-                          },
-                          lane);
-    }
+    float pv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pv[q] = -fp(ci, 4 * kq + q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[q], t[q], acc, 0, 0, 0);
+    return acc;
+}
+// Doubling BS -> 2 BS.  BS = 16: waves 0, 1 (U) and 4, 5 (L), one pair of
+// blocks each.  BS = 32: wave 4 tri + 2 ti + tc the 16x16 tile (ti, tc); a
+// barrier parts the reads of U12 (L21) from the writes in its place.
+template <int BS>
+__device__ __forceinline__ float inv_double(DmRow *Dm, int w, int lane)
+{
+    constexpr int NT = BS / 16;  // tiles per side
+    const int tri = w >> 2, item = w & 3;
+    const int p = BS == 16 ? 32 * item : 0, ti = BS == 16 ? 0 : item >> 1, tc = BS == 16 ? 0 : item & 1;
+    // the coupling block's rows and columns, and the triangle left of the
+    // inner product (rows) and inside it (columns)
+    const int ra = tri == 0 ? p : p + BS, cb = tri == 0 ? p + BS : p;
+    const bool on = BS == 32 || item < 2;
+    f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
     if (on) {
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq) T[(16 * ti + 4 * kq + qq) * BS + 16 * tc + ci] = acc[qq];
-    }
-    __syncthreads();
-    if (!on) {
-    } else if (tri == 0) {  // X12 = -X11 T, X11 upper
-        acc = mm16f32<BS>([&](int i, int m) {
-                              const int ii = 16 * ti + i;
-                              const float x = Dm[p + ii][p + m];
-                              return m >= ii ? x : 0.0f;
-                          },
-                          [&](int m, int c) { return T[m * BS + 16 * tc + c]; }, lane);
-    } else {         // X21 = -X22 T, X22 unit lower
-        acc = mm16f32<BS>([&](int i, int m) {
-                              const int ii = 16 * ti + i;
-                              const float x = Dm[p + BS + ii][p + BS + m];
-                              return m < ii ? x : (m == ii ? 1.0f : 0.0f);
-                          },
-                          [&](int m, int c) { return T[m * BS + 16 * tc + c]; }, lane);
-    }
-    __syncthreads();
-    if (on) {
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const int ii = 16 * ti + 4 * kq + qq, cc = 16 * tc + ci;
-            if (tri == 0) Dm[p + ii][p + BS + cc] = -acc[qq];
-            else Dm[p + BS + ii][p + cc] = -acc[qq];
+        for (int h = 0; h < NT; ++h) {
+            if (tri == 0 ? h < ti : h > ti) continue;  // a zero tile of the left triangle
+            const f32x4 t = mm16f32<BS>([&](int i, int m) { return Dm[ra + 16 * h + i][cb + m]; },
+                                        [&](int m, int c) { return tri_at(Dm, tri, cb + m, cb + 16 * tc + c); },
+                                        lane);
+            x = mm16_sub(x, [&](int i, int m) { return tri_at(Dm, tri, ra + 16 * ti + i, ra + 16 * h + m); }, t, lane);
         }
     }
-    __syncthreads();
+    if constexpr (BS == 32) __syncthreads();
+    float mx = 0.0f;
+    if (on) {
+        const int ci = lane & 15, kq = lane >> 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            Dm[ra + 16 * ti + 4 * kq + q][cb + 16 * tc + ci] = x[q];
+            mx = fmaxf(mx, fabsf(x[q]));
+        }
+    }
+    return mx;
 }
 
 struct TopArgs {
@@ -492,12 +438,11 @@ struct TopArgs {
 };
 
 // ======================================================================= k_top
-// LDS of the square's workgroup: the row tile, the diagonal block (FP32),
-// the inversion scratch and two small reduction areas.
+// LDS of the square's workgroup: the row tile, the diagonal block (FP32), the
+// waves' maxima and the check's flag.
 constexpr int TOP_TILE_BYTES = PT * NB_OUT * 2;
 constexpr int TOP_DM_BYTES = PT * (PT + 1) * 4;
-constexpr int TOP_TS_BYTES = 2048 * 4;
-constexpr int TOP_LDS_BYTES = TOP_TILE_BYTES + TOP_DM_BYTES + TOP_TS_BYTES + 64 + 16;
+constexpr int TOP_LDS_BYTES = TOP_TILE_BYTES + TOP_DM_BYTES + 32 + 16;
 
 // Workgroup r of the diagonal square (see the file comment).  lds: at least
 // TOP_LDS_BYTES, 16-byte aligned.
@@ -507,9 +452,8 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
     typedef typename pmma<T>::vec vec;
     T *tile = (T *)lds;
     DmRow *Dm = (DmRow *)(lds + TOP_TILE_BYTES);
-    float *Ts = (float *)(lds + TOP_TILE_BYTES + TOP_DM_BYTES);
-    float2 *red2 = (float2 *)(lds + TOP_TILE_BYTES + TOP_DM_BYTES + TOP_TS_BYTES);
-    int &sfail = *(int *)(lds + TOP_TILE_BYTES + TOP_DM_BYTES + TOP_TS_BYTES + 64);
+    float *red = (float *)(lds + TOP_TILE_BYTES + TOP_DM_BYTES);
+    int &sfail = *(int *)(lds + TOP_TILE_BYTES + TOP_DM_BYTES + 32);
     if (block_flag(&a.flags[FLAG_FAIL])) return;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, h = lane >> 5, l32 = lane & 31;
     const int W = a.W, nl = W / PT;
@@ -750,11 +694,6 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
         *(u32x4 *)&tile[tix(i, 64 * r + cc, W)] = st;
     }
 
-    // ---- triangular inverses in place in Dm: U^{-1} on and above the
-    // diagonal, L^{-1} (unit diagonal) below it.  Diagonal 8x8 blocks first,
-    // then three doublings (8 -> 16 -> 32 -> 64): for a pair of inverted
-    // diagonal blocks X11, X22 and the block U12 (L21) between them,
-    // X12 = -X11 (U12 X22) and X21 = -X22 (L21 X11).
     // U(r - 1, r + 1) requested now: leaf r - 1 forms it after handing over
     // U(r - 1, r), so a request before the diagonal factorisation could
     // still find the words unpublished and the wait after the inversion
@@ -763,27 +702,19 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
     if (have_pre)
         tissue4<4>(a.pub + (size_t)(r - 1) * PUB_LEAF + PUB_U12 + (r + 1) * 2048 + op_word(w, 0, h, l32, 0),
                    op_word(0, 1, 0, 0, 0), pre);
-    inv_diag8(Dm, w, lane);
+    // the triangular inverses, and the scale exponents for their split into
+    // halves from the largest entries (waves 0..3 U^{-1}, 4..7 L^{-1}, whose
+    // unit diagonal is not stored)
+    float mx = w < 4 ? 0.0f : 1.0f;
+    mx = fmaxf(mx, inv_diag16(Dm, w, lane));
     __syncthreads();
-    inv_double8(Dm, Ts, t);
-    inv_double_mfma<16>(Dm, Ts, w, lane);
-    inv_double_mfma<32>(Dm, Ts, w, lane);
-    // scale exponents of the two inverses for the split into halves
-    int su, sl;
-    {
-        float mu = 0.0f, ml = 1.0f;
-        static_assert(PT * PT % TOP_THREADS == 0, "whole rounds");
-#pragma unroll
-        for (int k = 0; k < PT * PT / TOP_THREADS; ++k) {
-            const int e = t + k * TOP_THREADS, i = e >> 6, j = e & 63;
-            const float v = fabsf(Dm[i][j]);
-            if (i <= j) mu = fmaxf(mu, v);
-            else ml = fmaxf(ml, v);
-        }
-        float2 m2 = block_max2<TOP_THREADS / 64>(make_float2(mu, ml), red2);
-        su = scale_exp(m2.x);
-        sl = scale_exp(m2.y);
-    }
+    mx = fmaxf(mx, inv_double<16>(Dm, w, lane));
+    __syncthreads();
+    mx = wave_max(fmaxf(mx, inv_double<32>(Dm, w, lane)));
+    if (lane == 0) red[w] = mx;
+    __syncthreads();
+    const int su = scale_exp(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+    const int sl = scale_exp(fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7])));
     // ---- what leaf r passes on.  U(r, r + 1) first, since the next leaf's
     // workgroup waits for it: waves 0 and 1 form it with the scaled halves of
     // L^{-1} in registers, while waves 2..7 publish (U^{-1})^T (scaled
@@ -813,7 +744,7 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
         for (int fm = 0; fm < 2; ++fm) {
             f32x16 acc = zero16();
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
+            for (int ks = 0; ks < 2 + 2 * fm; ++ks) {  // L^{-1} is zero beyond
                 acc = pmma<T>::op(opa(fm, ks, 0), tb[ks], acc);
                 acc = pmma<T>::op(opa(fm, ks, 1), tb[ks], acc);
             }
@@ -855,7 +786,7 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
 #pragma unroll
             for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) linv8(fm, ks, lah[fm][ks], lal[fm][ks]);
+                for (int ks = 0; ks < 2 + 2 * fm; ++ks) linv8(fm, ks, lah[fm][ks], lal[fm][ks]);
             if (r > 0) upd_range(r - 1, r, r + 1, w, have_pre);
             u12(r + 1, w, [&](int fm, int ks, int lo) { return lo ? lal[fm][ks] : lah[fm][ks]; });
         }
