@@ -846,8 +846,8 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
         const uint32_t tag = a.tag0 + (uint32_t)r;
         uint64_t *pr = a.pub + (size_t)r * PUB_LEAF;
         const float fu = ldexpf(1.0f, su);
-        for (int e = t - 128; e < 2048; e += TOP_THREADS - 128) {
-            // e = op_word(fm, ks, h, l32, q)
+        for (int x = t - 128; x < 1536; x += TOP_THREADS - 128) {  // the words that are not all zero
+            const int e = x < 512 ? x : x + 512;                   // = op_word(fm, ks, h, l32, q)
             const int q = e & 3, l32e = (e >> 2) & 31, he = (e >> 7) & 1, kse = (e >> 8) & 3, fme = e >> 10;
             const int j = 32 * fme + l32e, k = 16 * kse + 8 * he + 2 * q;
             const float v0 = k <= j ? Dm[k][j] * fu : 0.0f;
@@ -871,6 +871,9 @@ __device__ __forceinline__ void top_body(const TopArgs &a, int r, char *lds)
         *(u32x4 *)(iv + IH_LHI + (w * 64 + lane) * 8) = uhv;
         *(u32x4 *)(iv + IH_LLO + (w * 64 + lane) * 8) = ulv;
         __syncthreads();  // every read of Dm done
+        // the words of U^{-1} that are zero: for k_trsm only
+        *(uint32_t *)(iv + IH_UHI + 2 * (512 + t)) = 0;
+        *(uint32_t *)(iv + IH_ULO + 2 * (512 + t)) = 0;
         lop[w * 64 + lane] = uhv;
         lop[512 + w * 64 + lane] = ulv;
         if (t == 0) {
