@@ -392,93 +392,120 @@ struct GemmProb {
     int64_t ldc;
 };
 
-template <typename T, int TM, int TN, int WGM, int WGN, int KC>
-__global__ __launch_bounds__(WGM *WGN * 64) void k_gemm16_pair(GemmProb p1, GemmProb p2, int K,
-                                                               int *__restrict__ flags)
-{
-    if (block_flag(&flags[FLAG_FAIL])) return;
-    const int nt1 = (p1.M / TM) * (p1.N / TN), nt2 = (p2.M / TM) * (p2.N / TN);
-    int tile = xcd_tile(blockIdx.x, nt1 + nt2);
-    const GemmProb &p = tile < nt1 ? p1 : p2;
-    if (tile >= nt1) tile -= nt1;
-    int tm, tn;
-    grouped_tile(tile, p.M / TM, p.N / TN, tm, tn);
-    __shared__ __attribute__((aligned(16))) T lds[gemm16_lds_elems<TM, TN, KC>()];
-    gemm16_tile<T, TM, TN, WGM, WGN, KC>(tm * TM, tn * TN, K, (const T *)p.At, p.ldat, (const T *)p.B,
-                                         p.ldb, (T *)p.C, p.ldc, flags, lds);
-}
-
 // ========================================== Schur GEMM, FP32/FP64 matrix cores
-// 64x64 block tile, 4 waves of 32x32 (2x2 fragments of 16x16), KC = 16.
+// C -= At^T B for one or two problems with the same K (the two updates that
+// follow a panel are independent).  64x64 block tile, 4 waves of 32x32 (2x2
+// fragments of 16x16); K in chunks of 32 through two LDS buffers, the chunk
+// after next in registers.  A K = 64 launch is one memory round trip: its
+// operands, C and the flag are requested together; the LDS rows keep K
+// contiguous, padded by two (FP32: four) elements, so 16-byte stores and the
+// fragments' reads (16 rows x 4 k) are free of bank conflicts.  The fragments
+// are computed transposed (the A rows as the second operand), so a wave's C
+// accesses are runs of 16 rows.
+// Small launches are bound by that round trip, large ones by the matrix cores
+// (50 TFLOP/s at M = N = 1984, K = 1024).
+// Measured, FP64: one tile, K = 64: 10.3 -> 6.0 us; 225 tiles, K = 1024: 81 ->
+// 51 us; 961 tiles: 198 -> 162 us (from 16-wide chunks read without looking
+// ahead and stored element by element); the updates of n = 3000: 1460 -> 670 us
+// in half the launches.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gemm_mfma4(int M, int N, int K, const T *__restrict__ At,
-                                                    int64_t ldat, const T *__restrict__ B,
-                                                    int64_t ldb, T *__restrict__ C, int64_t ldc,
+__global__ __launch_bounds__(256) void k_gemm_mfma4(GemmProb p1, GemmProb p2, int K,
                                                     int *__restrict__ flags, int check_abort)
 {
     typedef typename mfma16x4<T>::acc_t acc_t;
-    constexpr int TM = 64, TN = 64, KC = 16;
-    __shared__ T As[KC][TM + 4];
-    __shared__ T Bs[KC][TN + 4];
-    if (check_abort && block_flag(&flags[FLAG_FAIL])) return;
-    const int ntm = M / TM, ntn = N / TN, nt = ntm * ntn;
-    int tile = blockIdx.x;
-    if ((nt & 7) == 0) tile = (blockIdx.x & 7) * (nt >> 3) + (blockIdx.x >> 3);
-    const int row0 = (tile % ntm) * TM, col0 = (tile / ntm) * TN;
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int TM = 64, KC = 32, CH = 16 / (int)sizeof(T), CPR = KC / CH;
+    constexpr int KP = KC + CH, NL = TM * CPR / 256;  // 16-byte chunks a thread and operand
+    __shared__ __attribute__((aligned(16))) T As[2][TM * KP];
+    __shared__ __attribute__((aligned(16))) T Bs[2][TM * KP];
+    __shared__ int s_flag;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
-    acc_t acc[2][2];
+    int fl = 0;
+    if (check_abort && tid == 0) fl = ld_flag(&flags[FLAG_FAIL]);
+    const int n1 = (p1.M / TM) * (p1.N / TM), n2 = (p2.M / TM) * (p2.N / TM);
+    int tile = xcd_tile(blockIdx.x, n1 + n2), tm, tn;
+    const bool second = tile >= n1;
+    const GemmProb &p = second ? p2 : p1;
+    grouped_tile(second ? tile - n1 : tile, p.M / TM, p.N / TM, tm, tn);
+    const T *At = (const T *)p.At + (int64_t)(tm * TM) * p.ldat;
+    const T *B = (const T *)p.B + (int64_t)(tn * TM) * p.ldb;
+    const int64_t ldat = p.ldat, ldb = p.ldb;
+    u32x4 ra[2][NL], rb[2][NL];
+    auto load = [&](u32x4 (&xa)[NL], u32x4 (&xb)[NL], int kk) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[a][b][q] = 0;
-    // loader: thread -> (row r = tid/4, k quad kq = (tid%4)*4)
-    const int lrow = tid >> 2, lkq = (tid & 3) * 4;
-    for (int kk = 0; kk < K; kk += KC) {
-        T va[4], vb[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            va[q] = At[(int64_t)(row0 + lrow) * ldat + kk + lkq + q];
-            vb[q] = B[(int64_t)(col0 + lrow) * ldb + kk + lkq + q];
+        for (int c = 0; c < NL; ++c) {
+            const int ch = tid + c * 256, r = ch / CPR, seg = (ch % CPR) * CH;
+            xa[c] = *(const u32x4 *)(At + r * ldat + kk + seg);
+            xb[c] = *(const u32x4 *)(B + r * ldb + kk + seg);
         }
-        __syncthreads();
+    };
+    auto stage = [&](int buf, const u32x4 (&xa)[NL], const u32x4 (&xb)[NL]) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            As[lkq + q][lrow] = va[q];
-            Bs[lkq + q][lrow] = vb[q];
+        for (int c = 0; c < NL; ++c) {
+            const int ch = tid + c * 256, r = ch / CPR, seg = (ch % CPR) * CH;
+            *(u32x4 *)&As[buf][r * KP + seg] = xa[c];
+            *(u32x4 *)&Bs[buf][r * KP + seg] = xb[c];
         }
-        __syncthreads();
+    };
+    load(ra[0], rb[0], 0);
+    load(ra[1], rb[1], KC);
+    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32, ci = lane & 15, kl = lane >> 4;
+    T *C = (T *)p.C + (int64_t)(tn * TM + wn) * p.ldc + tm * TM + wm + ci;
+    const int64_t ldc = p.ldc;
+    acc_t cv[2][2], acc[2][2];
+#pragma unroll
+    for (int fm = 0; fm < 2; ++fm)
+#pragma unroll
+        for (int fn = 0; fn < 2; ++fn)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                cv[fm][fn][q] = C[(fn * 16 + mfma16x4<T>::row(lane, q)) * ldc + fm * 16];
+                acc[fm][fn][q] = 0;
+            }
+    auto product = [&](int buf) {
 #pragma unroll
         for (int ks = 0; ks < KC; ks += 4) {
-            const int kr = ks + (lane >> 4), ci = lane & 15;
+            T a[2], b[2];
 #pragma unroll
-            for (int fm = 0; fm < 2; ++fm) {
-                const T a = As[kr][wm * 32 + fm * 16 + ci];
-#pragma unroll
-                for (int fn = 0; fn < 2; ++fn) {
-                    const T b = Bs[kr][wn * 32 + fn * 16 + ci];
-                    acc[fm][fn] = mfma16x4<T>::op(a, b, acc[fm][fn]);
-                }
+            for (int f = 0; f < 2; ++f) {
+                a[f] = As[buf][(wm + f * 16 + ci) * KP + ks + kl];
+                b[f] = Bs[buf][(wn + f * 16 + ci) * KP + ks + kl];
             }
+#pragma unroll
+            for (int fm = 0; fm < 2; ++fm)
+#pragma unroll
+                for (int fn = 0; fn < 2; ++fn)
+                    acc[fm][fn] = mfma16x4<T>::op(b[fn], a[fm], acc[fm][fn]);
+        }
+    };
+    stage(0, ra[0], rb[0]);
+    if (tid == 0) s_flag = fl;
+    __syncthreads();
+    if (s_flag) return;  // block-uniform
+    for (int kk = 0; kk < K; kk += 2 * KC) {
+        const bool more = kk + 2 * KC < K;
+        if (more) load(ra[0], rb[0], kk + 2 * KC);
+        product(0);
+        stage(1, ra[1], rb[1]);
+        __syncthreads();
+        if (more) load(ra[1], rb[1], kk + 3 * KC);
+        product(1);
+        if (more) {
+            stage(0, ra[0], rb[0]);
+            __syncthreads();
         }
     }
     bool bad = false;
 #pragma unroll
     for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-        for (int fn = 0; fn < 2; ++fn) {
-            const int col = col0 + wn * 32 + fn * 16 + (lane & 15);
-            const int rb0 = row0 + wm * 32 + fm * 16;
+        for (int fn = 0; fn < 2; ++fn)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                T *p = C + (int64_t)col * ldc + rb0 + mfma16x4<T>::row(lane, q);
-                const T v = *p - acc[fm][fn][q];
+                const T v = cv[fm][fn][q] - acc[fm][fn][q];
                 bad |= !isfinite((double)v);
-                *p = v;
+                C[(fn * 16 + mfma16x4<T>::row(lane, q)) * ldc + fm * 16] = v;
             }
-        }
     if (bad) set_flag(&flags[FLAG_NONFINITE], 1);
 }
 
@@ -512,8 +539,6 @@ hipError_t launch_leaf_spec2(int prec, int64_t Np, int64_t c0, void *A, int64_t 
                              hipStream_t s)
 {
     switch (prec) {
-    case N3P_FP16: return leaf_spec_t<f16>(Np, c0, A, lda, LT, k0, DG, DGprev, cprev, flags, s);
-    case N3P_BF16: return leaf_spec_t<bf16>(Np, c0, A, lda, LT, k0, DG, DGprev, cprev, flags, s);
     case N3P_FP32: return leaf_spec_t<float>(Np, c0, A, lda, LT, k0, DG, DGprev, cprev, flags, s);
     case N3P_FP64: return leaf_spec_t<double>(Np, c0, A, lda, LT, k0, DG, DGprev, cprev, flags, s);
     }
@@ -559,15 +584,23 @@ static hipError_t gemm16_t(int64_t M, int64_t N, int64_t K, const void *At, int6
 }
 
 template <typename T>
+static hipError_t gemm4_pair_t(GemmProb a, GemmProb b, int K, int *flags, bool ca, hipStream_t s)
+{
+    const unsigned g = (unsigned)((a.M / 64) * (a.N / 64) + (b.M / 64) * (b.N / 64));
+    hipLaunchKernelGGL(k_gemm_mfma4<T>, dim3(g), dim3(256), 0, s, a, b, K, flags, (int)ca);
+    return hipGetLastError();
+}
+
+template <typename T>
 static hipError_t gemm4_t(int64_t M, int64_t N, int64_t K, const void *At, int64_t ldat,
                           const void *B, int64_t ldb, void *C, int64_t ldc, int *flags, bool ca,
                           hipStream_t s)
 {
-    if (M % 64 || N % 64 || K % 16) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)((M / 64) * (N / 64));
-    hipLaunchKernelGGL(k_gemm_mfma4<T>, dim3(grid), dim3(256), 0, s, (int)M, (int)N, (int)K,
-                       (const T *)At, ldat, (const T *)B, ldb, (T *)C, ldc, flags, (int)ca);
-    return hipGetLastError();
+    if (M % 64 || N % 64 || K % 64) return hipErrorInvalidValue;
+    const GemmProb a{(int)M, (int)N, At, ldat, B, ldb, C, ldc};
+    GemmProb none = a;
+    none.M = 0;
+    return gemm4_pair_t<T>(a, none, (int)K, flags, ca, s);
 }
 
 hipError_t launch_gemm_sub(int prec, int64_t M, int64_t N, int64_t K, const void *At, int64_t ldat,
@@ -584,37 +617,23 @@ hipError_t launch_gemm_sub(int prec, int64_t M, int64_t N, int64_t K, const void
     return hipErrorInvalidValue;
 }
 
-template <typename T>
-static hipError_t gemm16_pair_t(GemmProb a, GemmProb b, int K, int *flags, hipStream_t s)
-{
-    auto fits = [](const GemmProb &q, int t) { return q.M % t == 0 && q.N % t == 0; };
-    if (fits(a, 128) && fits(b, 128)) {
-        const unsigned g = (unsigned)((a.M / 128) * (a.N / 128) + (b.M / 128) * (b.N / 128));
-        hipLaunchKernelGGL((k_gemm16_pair<T, 128, 128, 2, 2, 32>), dim3(g), dim3(256), 0, s, a, b, K, flags);
-    } else {
-        const unsigned g = (unsigned)((a.M / 64) * (a.N / 64) + (b.M / 64) * (b.N / 64));
-        hipLaunchKernelGGL((k_gemm16_pair<T, 64, 64, 2, 2, 32>), dim3(g), dim3(256), 0, s, a, b, K, flags);
-    }
-    return hipGetLastError();
-}
-
-// C1 -= At1^T B1 and C2 -= At2^T B2 (same K) in one launch; FP16/BF16 only,
-// every M, N a multiple of 64 and K of 32.  An empty problem is allowed.
+// C1 -= At1^T B1 and C2 -= At2^T B2 (same K) in one launch; FP32/FP64 only,
+// every M, N, K a multiple of 64.  An empty problem is allowed.
 hipError_t launch_gemm_pair(int prec, int64_t M1, int64_t N1, const void *At1, int64_t ldat1,
                             const void *B1, int64_t ldb1, void *C1, int64_t ldc1, int64_t M2,
                             int64_t N2, const void *At2, int64_t ldat2, const void *B2,
                             int64_t ldb2, void *C2, int64_t ldc2, int64_t K, int *flags,
                             hipStream_t s)
 {
-    if (M1 % 64 || N1 % 64 || M2 % 64 || N2 % 64 || K % 32 || K <= 0) return hipErrorInvalidValue;
+    if (M1 % 64 || N1 % 64 || M2 % 64 || N2 % 64 || K % 64 || K <= 0) return hipErrorInvalidValue;
     GemmProb a{(int)M1, (int)N1, At1, ldat1, B1, ldb1, C1, ldc1};
     GemmProb b{(int)M2, (int)N2, At2, ldat2, B2, ldb2, C2, ldc2};
     if (M1 <= 0 || N1 <= 0) { a.M = 0; a.N = 64; }
     if (M2 <= 0 || N2 <= 0) { b.M = 0; b.N = 64; }
     if (a.M == 0 && b.M == 0) return hipSuccess;
     switch (prec) {
-    case N3P_FP16: return gemm16_pair_t<f16>(a, b, (int)K, flags, s);
-    case N3P_BF16: return gemm16_pair_t<bf16>(a, b, (int)K, flags, s);
+    case N3P_FP32: return gemm4_pair_t<float>(a, b, (int)K, flags, true, s);
+    case N3P_FP64: return gemm4_pair_t<double>(a, b, (int)K, flags, true, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -145,7 +145,6 @@ int getrf_spec(const FactorWs &f, hipStream_t s)
     char *LT = (char *)f.LT;
     char *DG = (char *)f.DG;
     const size_t dgb = (size_t)NB_LEAF * NB_LEAF * es;
-    const bool mfma16 = prec == N3P_FP16 || prec == N3P_BF16;
     auto at = [&](int64_t i, int64_t j) { return (void *)(A + ((size_t)i + (size_t)j * lda) * es); };
     // C(r0.., c0..) of the two updates (r0 = first row below the source
     // panel, [cb, ce) its block's columns): the rest of the block below the
@@ -153,17 +152,9 @@ int getrf_spec(const FactorWs &f, hipStream_t s)
     // K columns from kc within the outer block; B: the panel's U rows.
     auto update = [&](int64_t r0, int64_t ce, int64_t prow, int64_t kc, int64_t K) -> int {
         const void *At = LT + ((size_t)r0 * NB_OUT + (size_t)kc) * es;
-        if (mfma16) {
-            HIPCHK(launch_gemm_pair(prec, Np - r0, ce - r0, At, NB_OUT, at(prow, r0), lda,
-                                    at(r0, r0), lda, ce - r0, Np - ce, At, NB_OUT, at(prow, ce),
-                                    lda, at(r0, ce), lda, K, f.flags, s));
-        } else {
-            HIPCHK(launch_gemm_sub(prec, Np - r0, ce - r0, K, At, NB_OUT, at(prow, r0), lda,
-                                   at(r0, r0), lda, f.flags, true, s));
-            if (ce < Np)
-                HIPCHK(launch_gemm_sub(prec, ce - r0, Np - ce, K, At, NB_OUT, at(prow, ce), lda,
-                                       at(r0, ce), lda, f.flags, true, s));
-        }
+        HIPCHK(launch_gemm_pair(prec, Np - r0, ce - r0, At, NB_OUT, at(prow, r0), lda, at(r0, r0),
+                                lda, ce - r0, Np - ce, At, NB_OUT, at(prow, ce), lda, at(r0, ce),
+                                lda, K, f.flags, s));
         return 0;
     };
     for (int64_t k0 = 0; k0 < Np; k0 += NB_OUT) {
