@@ -29,28 +29,6 @@
 
 namespace n3p {
 
-// oct_bcast<K>: value held by lane K of each group of eight lanes.  A quad
-// broadcast gives every quad its own lane K % 4; the quad of the octet that
-// does not hold lane K then takes it from its neighbour quad by a row shift of
-// four lanes, written only to that quad's banks.
-template <int K> __device__ __forceinline__ int oct_bcast_i(int v)
-{
-    const int qb = __builtin_amdgcn_mov_dpp(v, (K & 3) * 0x55, 0xF, 0xF, false);
-    if (K < 4) return __builtin_amdgcn_update_dpp(qb, qb, 0x114, 0xF, 0xA, false);  // row_shr:4
-    return __builtin_amdgcn_update_dpp(qb, qb, 0x104, 0xF, 0x5, false);             // row_shl:4
-}
-template <int K> __device__ __forceinline__ float oct_bcast(float v)
-{
-    return __int_as_float(oct_bcast_i<K>(__float_as_int(v)));
-}
-template <int K> __device__ __forceinline__ double oct_bcast(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = oct_bcast_i<K>((int)(b & 0xffffffffLL));
-    const int hi = oct_bcast_i<K>((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // recip: 1/v.  FP32: hardware reciprocal estimate refined by one Newton-Raphson
 // step (r + r(1 - v r)), within an ulp of the rounded quotient; FP64: division.
 __device__ __forceinline__ float recip(float v)
@@ -64,23 +42,51 @@ __device__ __forceinline__ double recip(double v) { return 1.0 / v; }
 // Tile b < nrt: 64 rows of L21 below the leaf; nrt <= b < nrt + nct: 64
 // columns of the U row block to the right of the leaf (when the leaf is the
 // last one, a single tile only stores the diagonal block).  Every workgroup
-// first factors the 64x64 diagonal block itself (identical arithmetic in
-// every workgroup), so none waits for another.  The factored diagonal block
-// goes to DG (a side buffer): workgroups still reading the unfactored block
-// from A must not see it change; with DG null (allowed only when the leaf has
-// no tiles) it goes straight to A.  DGprev (if non-null) is the previous
-// leaf's diagonal block, copied into A by tile 0 (nothing else touches that
-// region now).  L21 is also written transposed to LT (row i at
-// LT + i * ldlt + ltcol, K contiguous) for the Schur update.
+// factors the 64x64 diagonal block itself (identical arithmetic in every
+// workgroup), so none waits for another.  The factored diagonal block goes to
+// DG (a side buffer): workgroups still reading the unfactored block from A
+// must not see it change; with DG null (allowed only when the leaf has no
+// tiles) it goes straight to A.  DGprev (if non-null) is the previous leaf's
+// diagonal block, copied into A by tile 0 (nothing else touches that region
+// now).  L21 is also written transposed to LT (row i at LT + i * ldlt + ltcol,
+// K contiguous) for the Schur update.
 //
-// Every column step is a short dependent chain, so the work stays on the
-// VALU path: the diagonal LU is blocked by 8-column strips held one row per
-// lane (readlane broadcasts, one barrier per strip); the triangular solves
-// use eight lanes per row or column (DPP broadcasts, no barrier).  Column
-// loops run in groups whose index is a runtime loop while the steps inside
-// are unrolled; per-lane register arrays rotate after each group so every
-// register index stays static.
+// The chain of 64 column steps bounds the leaf, so the tile rides along it: a
+// wavefront holds 8 columns of the diagonal block and of the L21 rows (or 8
+// rows of the block and of the U12 columns), one row (column) per lane, and
+// the broadcasts that eliminate the block serve the tile as well.  Panels of 8
+// steps pass from wavefront to wavefront through LDS, one barrier each.  A
+// solve of the tile after the block's factorisation cost another 10 us (its
+// coefficients, 64 per lane and group of 8 steps, kept the LDS busy).  The
+// panel loop is unrolled for constant lanes in the broadcasts (FP64: 20 -> 17
+// us).  Measured: k_leaf_spec<double> 29.2 -> 17.1 us (2 and 92 tiles alike);
+// the batched FP16 leaf 25 -> 17 us, 35 -> 32 us with four tiles a CU.
 constexpr int LEAF_THREADS = 512;
+
+// eight consecutive elements (16-byte aligned) to and from the compute type
+template <typename T, typename CT> __device__ __forceinline__ void load8(const T *src, CT (&v)[8])
+{
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int CH = 16 / (int)sizeof(T);
+#pragma unroll
+    for (int q = 0; q < 8 / CH; ++q) {
+        const vec e = *(const vec *)(src + q * CH);
+#pragma unroll
+        for (int u = 0; u < CH; ++u) v[q * CH + u] = (CT)to_f32((T)e[u]);
+    }
+}
+template <typename T, typename CT> __device__ __forceinline__ void store8(T *dst, const CT (&v)[8])
+{
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int CH = 16 / (int)sizeof(T);
+#pragma unroll
+    for (int q = 0; q < 8 / CH; ++q) {
+        vec e;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) e[u] = to_store_d<T>((double)v[q * CH + u]);
+        *(vec *)(dst + q * CH) = e;
+    }
+}
 
 template <typename T>
 __device__ __forceinline__ void leaf_body(int bid, int64_t Np, int64_t c0, T *__restrict__ A,
@@ -90,252 +96,179 @@ __device__ __forceinline__ void leaf_body(int bid, int64_t Np, int64_t c0, T *__
                                           int *__restrict__ flags)
 {
     typedef typename compute_of<T>::type CT;
-    constexpr int L = NB_LEAF;
-    constexpr int LP = L + 5;  // staging row stride: column chunks conflict-free, octet accesses 2-way
-    constexpr int NT = LEAF_THREADS;
-    // diagonal block; odd row stride, so the column accesses (lane = row)
-    // of the strips hit 64 different banks
-    __shared__ __attribute__((aligned(16))) CT Dm[L][L + 1];
-    // Per column group kc of the tile solves: Ui[kc][kq][g][c] =
-    // U[8kc+kq][8(kc+c)+g] and Li[kc][kq][g][u] = L[8(kc+u)+g][8kc+kq] where
-    // kc + c <= 7 and that index exceeds the row (column) 8kc+kq, else 0 -- so
-    // a lane's 8 coefficients of one step are contiguous and 16-byte aligned.
-    __shared__ __attribute__((aligned(16))) CT Ui[L * L];
-    __shared__ __attribute__((aligned(16))) CT Li[L * L];
-    __shared__ __attribute__((aligned(16))) CT Sg[L][LP];       // staging of one tile
-    __shared__ CT rdiag[L];
-    __shared__ int sfail;
-    if (block_flag(&flags[FLAG_FAIL])) return;
-    const int t = threadIdx.x;
-    if (bid == 0 && DGprev) {
-        for (int e = t; e < L * L; e += NT) {
-            const int i = e % L, j = e / L;
-            A[(cprev + i) + (cprev + j) * lda] = DGprev[i + j * L];
-        }
-    }
-    if (t == 0) sfail = 0;
-    constexpr int CH = 16 / (int)sizeof(T);  // elements per 16-byte chunk
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    union Chunk { u32x4 v; T e[CH]; };
-    for (int e = t; e < L * L / CH; e += NT) {  // diagonal block, column chunks
-        const int i0 = (e % (L / CH)) * CH, j = e / (L / CH);
-        Chunk ch;
-        ch.v = *(const u32x4 *)(A + (c0 + i0) + (c0 + j) * lda);
-#pragma unroll
-        for (int u = 0; u < CH; ++u) Dm[i0 + u][j] = (CT)to_f32(ch.e[u]);
-    }
-    // this workgroup's tile (64 rows of L21 or 64 columns of U12), loaded now
-    // into registers so the loads overlap the diagonal factorisation
-    constexpr int NPRE = L * L / CH / NT;
-    const T *tsrc = nullptr;
-    if (bid < nrt) tsrc = A + (c0 + L + (int64_t)bid * L) + c0 * lda;
-    else if (bid - nrt < nct) tsrc = A + c0 + (c0 + L + (int64_t)(bid - nrt) * L) * lda;
-    u32x4 pre[NPRE];
-    if (tsrc) {
-#pragma unroll
-        for (int k = 0; k < NPRE; ++k) {
-            const int e = t + k * NT, i0 = (e % (L / CH)) * CH, j = e / (L / CH);
-            pre[k] = *(const u32x4 *)(tsrc + i0 + j * lda);
-        }
-    }
-    __syncthreads();
+    constexpr int L = NB_LEAF, NT = LEAF_THREADS;
+    // step k: the block's multipliers by row (its U row by column), and the
+    // tile's L21 column (its U12 row)
+    __shared__ CT Pm[L][L];
+    __shared__ CT Zm[L][L];
+    __shared__ CT rs[L];
+    __shared__ int sfail, s_flag;
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    int fl = 0;
+    if (t == 0) fl = ld_flag(&flags[FLAG_FAIL]);
     const CT margin = (CT)(1.0 - 1.0 / 256.0);
-    // ---- diagonal block, no interchange, with the partial-pivoting check.
-    // Blocked by 8-column strips: wave w keeps columns 8w .. 8w+7 of all 64
-    // rows in registers (lane = row).  For panel p, wave p factors its strip
-    // (pivot row entries by readlane, no barrier inside the panel) and stores
-    // it; after one barrier every later wave applies the panel to its own
-    // strip: row k of the strip is final when step k starts, so it is read
-    // by readlane and the multipliers of the panel come from LDS.
-    {
-        const int w = t / 64, r = t % 64;
-        CT x[8];
+    bool bad = false;
+    CT x[8], z[8];
+    if (bid < nrt || nrt == 0) {
+        // ---- 64 rows [R0, R0+64) of L21, lane = row.  Wave w keeps columns
+        // 8w .. 8w+7 of the block (x) and of the tile (z); the pivot row's
+        // entries come by readlane.  An entry of the tile is checked against
+        // the pivot when its column is eliminated: the Schur complement entry
+        // that partial pivoting would compare.
+        const int64_t R0 = c0 + L + (int64_t)bid * L;
+        const bool tile = bid < nrt;
+        T dp[L * L / NT];
+        if (bid == 0 && DGprev) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) x[c] = Dm[r][8 * w + c];
-        bool fail = false;
+            for (int q = 0; q < L * L / NT; ++q) dp[q] = DGprev[t + q * NT];
+        }
+        T *Dc = A + (c0 + lane) + (c0 + 8 * w) * lda, *Zc = A + (R0 + lane) + (c0 + 8 * w) * lda;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            x[c] = (CT)to_f32(Dc[c * lda]);
+            z[c] = tile ? (CT)to_f32(Zc[c * lda]) : (CT)0;
+        }
+        if (t == 0) {
+            s_flag = fl;
+            sfail = 0;
+        }
+        bool fail = false, zfail = false;
+#pragma unroll
         for (int p = 0; p < 8; ++p) {
             if (w == p) {
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) {
                     const int k = 8 * p + kk;
-                    // branch-free (selects, no exec-mask branches): this is the
-                    // leaf's serial chain
+                    // branch-free (selects, no exec-mask branches), and every
+                    // broadcast before the updates: this is the leaf's serial chain
                     const CT piv = lane_bcast(x[kk], k);
                     const CT rp = recip(piv);
-                    const bool below = r > k;
+                    const bool below = lane > k;
+                    const CT lim = margin * fabs(piv);
+                    fail |= !(fabs(piv) > (CT)0) || (below && !(fabs(x[kk]) <= lim));
+                    zfail |= !(fabs(z[kk]) <= lim);
                     const CT lx = x[kk] * rp;
-                    fail |= !(fabs(piv) > (CT)0) || (below && !(fabs(x[kk]) <= margin * fabs(piv)));
                     const CT l = below ? lx : (CT)0;
                     x[kk] = below ? lx : x[kk];
+                    z[kk] *= (CT)1 / piv;
+                    Pm[k][lane] = l;
+                    Zm[k][lane] = z[kk];
+                    CT ub[8];
 #pragma unroll
-                    for (int c = kk + 1; c < 8; ++c) x[c] -= l * lane_bcast(x[c], k);
+                    for (int c = kk + 1; c < 8; ++c) ub[c] = lane_bcast(x[c], k);
+#pragma unroll
+                    for (int c = kk + 1; c < 8; ++c) {
+                        x[c] -= l * ub[c];
+                        z[c] -= z[kk] * ub[c];
+                    }
                 }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) Dm[r][8 * p + c] = x[c];
             }
             __syncthreads();
+            if (p == 0 && s_flag) return;  // block-uniform
             if (w > p) {
-                CT l[8];
+                CT l[8], zl[8];
 #pragma unroll
-                for (int kk = 0; kk < 8; ++kk) l[kk] = r > 8 * p + kk ? Dm[r][8 * p + kk] : (CT)0;
+                for (int kk = 0; kk < 8; ++kk) {
+                    l[kk] = Pm[8 * p + kk][lane];
+                    zl[kk] = Zm[8 * p + kk][lane];
+                }
 #pragma unroll
-                for (int kk = 0; kk < 8; ++kk)
+                for (int kk = 0; kk < 8; ++kk) {
+                    CT ub[8];
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) x[c] -= l[kk] * lane_bcast(x[c], 8 * p + kk);
+                    for (int c = 0; c < 8; ++c) ub[c] = lane_bcast(x[c], 8 * p + kk);
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        x[c] -= l[kk] * ub[c];
+                        z[c] -= zl[kk] * ub[c];
+                    }
+                }
             }
         }
         if (fail) sfail = 1;
-    }
-    __syncthreads();
-    if (sfail) {  // block-uniform: settled before the barrier
-        if (t == 0) set_flag(&flags[FLAG_FAIL], 1);
-        return;
-    }
-    for (int e = t; e < L * L; e += NT) {
-        const int c = e % 8, g = (e / 8) % 8, kq = (e / 64) % 8, kc = e / 512;
-        const int k = 8 * kc + kq, j = 8 * (kc + c) + g;
-        const bool in = kc + c <= 7 && j > k;
-        Ui[e] = in ? Dm[k][j] : (CT)0;
-        Li[e] = in ? Dm[j][k] : (CT)0;
-    }
-    if (t < L) rdiag[t] = (CT)1 / Dm[t][t];
-    if (bid == 0) {
-        for (int e = t; e < L * L; e += NT) {
-            const int i = e % L, j = e / L;
-            const T v = to_store_d<T>((double)Dm[i][j]);
-            if (DG) DG[i + j * L] = v;
-            else A[(c0 + i) + (c0 + j) * lda] = v;
-        }
-    }
-    __syncthreads();
-    const int g = t % 8, w8 = t / 8;  // lane-in-octet, octet index (row or column)
-    bool bad = false, fail = false;
-    if (bid < nrt) {
-        // ---- L21 rows [R0, R0+64): l U11 = a.  Octet w8 owns row R0 + w8;
-        // lane g holds columns 8(c + kc) + g of the current group kc.  At step
-        // k the owner lane (g = k % 8, slot 0) holds the Schur complement entry
-        // partial pivoting would compare: it checks it against the pivot,
-        // scales it and broadcasts it to its octet.
-        const int64_t R0 = c0 + L + (int64_t)bid * L;
-#pragma unroll
-        for (int k = 0; k < NPRE; ++k) {  // the prefetched column chunks
-            const int e = t + k * NT, i0 = (e % (L / CH)) * CH, j = e / (L / CH);
-            Chunk ch;
-            ch.v = pre[k];
-#pragma unroll
-            for (int u = 0; u < CH; ++u) Sg[i0 + u][j] = (CT)to_f32(ch.e[u]);
-        }
         __syncthreads();
-        CT x[8];
+        if (sfail) {  // block-uniform: settled before the barrier
+            if (t == 0) set_flag(&flags[FLAG_FAIL], 1);
+            return;
+        }
+        if (bid == 0) {
+            if (DGprev) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) x[c] = Sg[w8][8 * c + g];
-        for (int kc = 0; kc < 8; ++kc) {
-            CT u[8][8];
-#pragma unroll
-            for (int kq = 0; kq < 8; ++kq)
-#pragma unroll
-                for (int c = 0; c < 8; ++c) u[kq][c] = Ui[((kc * 8 + kq) * 8 + g) * 8 + c];
-            // this lane owns column 8kc + g: its pivot bound and reciprocal
-            const CT lim = margin * fabs(Dm[8 * kc + g][8 * kc + g]);
-            const CT rd = rdiag[8 * kc + g];
-#pragma unroll
-            for (int kq = 0; kq < 8; ++kq) {
-                const bool own = g == kq;  // branch-free, as in the diagonal chain
-                fail |= own && !(fabs(x[0]) <= lim);
-                x[0] = own ? x[0] * rd : x[0];
-                CT xk;
-                switch (kq) {
-                case 0: xk = oct_bcast<0>(x[0]); break;
-                case 1: xk = oct_bcast<1>(x[0]); break;
-                case 2: xk = oct_bcast<2>(x[0]); break;
-                case 3: xk = oct_bcast<3>(x[0]); break;
-                case 4: xk = oct_bcast<4>(x[0]); break;
-                case 5: xk = oct_bcast<5>(x[0]); break;
-                case 6: xk = oct_bcast<6>(x[0]); break;
-                default: xk = oct_bcast<7>(x[0]); break;
+                for (int q = 0; q < L * L / NT; ++q) {
+                    const int e = t + q * NT;
+                    A[(cprev + e % L) + (cprev + e / L) * lda] = dp[q];
                 }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) x[c] -= xk * u[kq][c];
             }
-            Sg[w8][8 * kc + g] = x[0];
+            T *out = DG ? DG + lane + 8 * w * L : Dc;
+            const int64_t ldo = DG ? L : lda;
 #pragma unroll
-            for (int c = 0; c < 7; ++c) x[c] = x[c + 1];
-            x[7] = 0;
+            for (int c = 0; c < 8; ++c) out[c * ldo] = to_store_d<T>((double)x[c]);
         }
-        __syncthreads();
-        for (int e = t; e < L * L / CH; e += NT) {  // A: column chunks
-            const int i0 = (e % (L / CH)) * CH, j = e / (L / CH);
-            Chunk ch;
+        if (!tile) return;
 #pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                ch.e[u] = to_store_d<T>((double)Sg[i0 + u][j]);
-                bad |= !isfinite(to_f32(ch.e[u]));  // the stored value
-            }
-            *(u32x4 *)(A + (R0 + i0) + (c0 + j) * lda) = ch.v;
+        for (int c = 0; c < 8; ++c) {
+            const T v = to_store_d<T>((double)z[c]);
+            bad |= !isfinite(to_f32(v));  // the stored value
+            Zc[c * lda] = v;
         }
-        for (int e = t; e < L * L / CH; e += NT) {  // LT: row chunks (K contiguous)
-            const int i = e / (L / CH), j0 = (e % (L / CH)) * CH;
-            Chunk ch;
-#pragma unroll
-            for (int u = 0; u < CH; ++u) ch.e[u] = to_store_d<T>((double)Sg[i][j0 + u]);
-            *(u32x4 *)(LT + (R0 + i) * ldlt + ltcol + j0) = ch.v;
-        }
-        if (fail) set_flag(&flags[FLAG_FAIL], 1);
-    } else if (bid - nrt < nct) {
-        // ---- U12 columns [C0, C0+64): forward substitution with the unit
-        // lower L11.  Octet w8 owns column C0 + w8; lane g holds rows
-        // 8(u + ku) + g of the current group ku.
+        store8(LT + (R0 + lane) * ldlt + ltcol + 8 * w, z);
+        if (zfail) set_flag(&flags[FLAG_FAIL], 1);
+    } else {
+        // ---- 64 columns [C0, C0+64) of U12, lane = column.  Wave w keeps
+        // rows 8w .. 8w+7 of the block (x) and of the tile (z); the multiplier
+        // of row i at step k is lane k's entry of that row over the pivot, the
+        // same product as above.  The block is checked by the L21 tiles.
         const int64_t C0 = c0 + L + (int64_t)(bid - nrt) * L;
+        load8(A + c0 + 8 * w + (c0 + lane) * lda, x);
+        load8(A + c0 + 8 * w + (C0 + lane) * lda, z);
+        if (t == 0) s_flag = fl;
 #pragma unroll
-        for (int k = 0; k < NPRE; ++k) {  // the prefetched column chunks
-            const int e = t + k * NT, i0 = (e % (L / CH)) * CH, j = e / (L / CH);
-            Chunk ch;
-            ch.v = pre[k];
+        for (int p = 0; p < 8; ++p) {
+            if (w == p) {
 #pragma unroll
-            for (int u = 0; u < CH; ++u) Sg[i0 + u][j] = (CT)to_f32(ch.e[u]);
-        }
-        __syncthreads();
-        CT y[8];
+                for (int kk = 0; kk < 8; ++kk) {
+                    const int k = 8 * p + kk;
+                    const CT rp = recip(lane_bcast(x[kk], k));
+                    const CT u = lane > k ? x[kk] : (CT)0;
+                    Pm[k][lane] = u;
+                    Zm[k][lane] = z[kk];
+                    if (lane == 0) rs[k] = rp;
+                    CT l[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) y[u] = Sg[8 * u + g][w8];
-        for (int ku = 0; ku < 8; ++ku) {
-            CT lv[8][8];
+                    for (int c = kk + 1; c < 8; ++c) l[c] = lane_bcast(x[c], k) * rp;
 #pragma unroll
-            for (int kq = 0; kq < 8; ++kq)
+                    for (int c = kk + 1; c < 8; ++c) {
+                        x[c] -= l[c] * u;
+                        z[c] -= l[c] * z[kk];
+                    }
+                }
+            }
+            __syncthreads();
+            if (p == 0 && s_flag) return;  // block-uniform
+            if (w > p) {
+                CT u[8], zu[8], rk[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) lv[kq][u] = Li[((ku * 8 + kq) * 8 + g) * 8 + u];
-#pragma unroll
-            for (int kq = 0; kq < 8; ++kq) {
-                CT yk;
-                switch (kq) {
-                case 0: yk = oct_bcast<0>(y[0]); break;
-                case 1: yk = oct_bcast<1>(y[0]); break;
-                case 2: yk = oct_bcast<2>(y[0]); break;
-                case 3: yk = oct_bcast<3>(y[0]); break;
-                case 4: yk = oct_bcast<4>(y[0]); break;
-                case 5: yk = oct_bcast<5>(y[0]); break;
-                case 6: yk = oct_bcast<6>(y[0]); break;
-                default: yk = oct_bcast<7>(y[0]); break;
+                for (int kk = 0; kk < 8; ++kk) {
+                    u[kk] = Pm[8 * p + kk][lane];
+                    zu[kk] = Zm[8 * p + kk][lane];
+                    rk[kk] = rs[8 * p + kk];
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) y[u] -= lv[kq][u] * yk;
-            }
-            Sg[8 * ku + g][w8] = y[0];
+                for (int kk = 0; kk < 8; ++kk) {
+                    CT l[8];
 #pragma unroll
-            for (int u = 0; u < 7; ++u) y[u] = y[u + 1];
-            y[7] = 0;
-        }
-        __syncthreads();
-        for (int e = t; e < L * L / CH; e += NT) {
-            const int i0 = (e % (L / CH)) * CH, j = e / (L / CH);
-            Chunk ch;
+                    for (int c = 0; c < 8; ++c) l[c] = lane_bcast(x[c], 8 * p + kk) * rk[kk];
 #pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                ch.e[u] = to_store_d<T>((double)Sg[i0 + u][j]);
-                bad |= !isfinite(to_f32(ch.e[u]));  // the stored value
+                    for (int c = 0; c < 8; ++c) {
+                        x[c] -= l[c] * u[kk];
+                        z[c] -= l[c] * zu[kk];
+                    }
+                }
             }
-            *(u32x4 *)(A + (c0 + i0) + (C0 + j) * lda) = ch.v;
         }
+        store8(A + c0 + 8 * w + (C0 + lane) * lda, z);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) bad |= !isfinite(to_f32(to_store_d<T>((double)z[c])));
     }
     if (bad) set_flag(&flags[FLAG_NONFINITE], 1);
 }
@@ -665,9 +598,8 @@ __global__ __launch_bounds__(LEAF_THREADS) void k_b_leaf(const BDesc *__restrict
     __shared__ int off[B_MAX_SLOTS + 1];
     const int64_t c0 = (int64_t)leaf * NB_LEAF;
     const int total = b_offsets(nslots, off, [&](int s) {
-        if (st[s].phase != BP_RUN || !st[s].factor || d[s].Np <= c0) return 0;
-        const int nrt = (int)((d[s].Np - c0 - NB_LEAF) / NB_LEAF);
-        return nrt > 0 ? 2 * nrt : 1;
+        const int nl = b_factor_leaves(d[s], st[s]) - leaf;
+        return nl > 1 ? 2 * (nl - 1) : std::max(nl, 0);
     });
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
         const int s = b_find(off, nslots, item);
@@ -694,8 +626,7 @@ __global__ __launch_bounds__(256) void k_b_gemm(const BDesc *__restrict__ d,
     __shared__ __attribute__((aligned(16))) T lds[gemm16_lds_elems<TM, TM, KC>()];
     const int64_t c0 = (int64_t)leaf * NB_LEAF, c1 = c0 + NB_LEAF;
     const int total = b_offsets(nslots, off, [&](int s) {
-        if (st[s].phase != BP_RUN || !st[s].factor || d[s].Np <= c1) return 0;
-        const int m = (int)((d[s].Np - c1) / TM);
+        const int m = std::max(b_factor_leaves(d[s], st[s]) - leaf - 1, 0);
         return m * m;
     });
     for (int item = blockIdx.x; item < total; item += gridDim.x) {

@@ -662,7 +662,8 @@ __global__ __launch_bounds__(256) void k_b_residual(const BDesc *__restrict__ d,
     __shared__ double red[HR][257];
     __shared__ int off[B_MAX_SLOTS + 1];
     const int total = b_offsets(nslots, off, [&](int s) {
-        return (mask >> st[s].phase & 1) ? (int)((d[s].n + HR - 1) / HR) : 0;
+        const int nb = (int)((d[s].n + HR - 1) / HR);
+        return (mask >> st[s].phase & 1) ? nb : 0;
     });
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
         const int s = b_find(off, nslots, item);
@@ -738,7 +739,7 @@ __global__ __launch_bounds__(256) void k_b_jac(const BDesc *__restrict__ d,
     __shared__ float sh[256];
     __shared__ int off[B_MAX_SLOTS + 1];
     const int total = b_offsets(nslots, off, [&](int s) {
-        return (st[s].phase == BP_RUN && st[s].factor) ? (int)d[s].Np : 0;
+        return b_factor_leaves(d[s], st[s]) * NB_LEAF;
     });
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
         const int s = b_find(off, nslots, item);

@@ -995,7 +995,8 @@ __global__ __launch_bounds__(256) void k_b_trsv(const BDesc *__restrict__ d,
     // of items on the levels before each
     int nb = 0;
     if (t < nslots) {
-        if (st[t].phase == BP_RUN && st[t].factor && st[t].ir_on) nb = (int)(d[t].Np / BS);
+        const int on = st[t].ir_on != 0, nl = b_factor_leaves(d[t], st[t]);
+        nb = on * nl * (NB_LEAF / BS);
         nbs[t] = nb;
     }
     __syncthreads();
@@ -1057,7 +1058,8 @@ __global__ __launch_bounds__(MV_NT) void k_b_gemv(const BDesc *__restrict__ d,
     __shared__ int off[B_MAX_SLOTS + 1];
     __shared__ double sh[MV_NT / 64][MV_RB];
     const int total = b_offsets(nslots, off, [&](int s) {
-        return (st[s].phase == BP_RUN && st[s].factor && st[s].ir_on) ? (int)(d[s].Np / MV_RB) : 0;
+        const int on = st[s].ir_on != 0, nl = b_factor_leaves(d[s], st[s]);
+        return on * nl * (NB_LEAF / MV_RB);
     });
     const int t = threadIdx.x;
     for (int item = blockIdx.x; item < total; item += gridDim.x) {

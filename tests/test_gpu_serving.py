@@ -201,3 +201,24 @@ def test_autotune_then_solve(env):
         assert rep.status == 0 and rep.its in (its_ref, its_ref + 1)
         assert rel_err(x.cpu().numpy(), xr) <= 1e-9
     eng.close()
+
+
+@pytest.mark.parametrize("count", [64, 65, 130])
+def test_engine_more_slots_than_a_wavefront(env, count):
+    """The items of a batched launch are counted 64 slots at a time: one full
+    chunk, one slot over, and three chunks of slots of one to five leaves."""
+    n3p, torch = env
+    reqs = [([64, 65, 130, 257][i % 4], [0.5, 0.9, 0.99][i % 3]) for i in range(count)]
+    print("case engine %d slots" % count, flush=True)
+    cfg = n3p.EngineConfig.default(max_slots=count, max_n=512)
+    eng = n3p.Engine(make_pool(n3p, torch, [n for n, _ in reqs], count), cfg)
+    slots = [eng.admit(n, c) for n, c in reqs]
+    assert None not in slots
+    run_to_completion(eng, slots)
+    for (n, c), s in zip(reqs, slots):
+        x = torch.empty(n, dtype=torch.float64, device="cuda")
+        rep = eng.collect(s, x)
+        xr, its_ref = oracle_ref(n, c)
+        assert rep.status == 0 and rep.its in (its_ref, its_ref + 1), (s, n, c)
+        assert rel_err(x.cpu().numpy(), xr) <= 1e-9, (s, n, c)
+    eng.close()
