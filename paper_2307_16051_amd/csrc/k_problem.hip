@@ -521,7 +521,8 @@ __global__ __launch_bounds__(256) void k_sumsq_part(int64_t n, const V *__restri
 }
 
 __global__ __launch_bounds__(256) void k_sum_sqrt(int m, const double *__restrict__ part,
-                                                  double *__restrict__ out)
+                                                  double *__restrict__ out,
+                                                  uint64_t *__restrict__ stamp)
 {
     __shared__ double sh[256];
     const int t = threadIdx.x;
@@ -533,10 +534,94 @@ __global__ __launch_bounds__(256) void k_sum_sqrt(int m, const double *__restric
         if (t < w) sh[t] += sh[t + w];
         __syncthreads();
     }
-    if (t == 0) out[0] = sqrt(sh[0]);
+    if (t == 0) {
+        out[0] = sqrt(sh[0]);
+        if (stamp) *stamp = __builtin_amdgcn_s_memrealtime();
+    }
 }
 
 constexpr int NRM_BLOCKS = 256;
+
+// The same norm by one workgroup, n <= NRM_ONE_N: a wavefront takes a chunk of
+// 256 elements (four loads a lane, up to four chunks in flight) and adds it in
+// the order of the block sums above, so the result is the same to the last
+// bit.  val(i) gives element i < n.  A launch instead of two, 3 us at n = 1000
+// and 4 us at n = 16384 against 4 + 4 us and the gap between them; beyond,
+// one workgroup's loads bound it (256 KiB take longer than the second launch).
+constexpr int NRM_ONE_NT = 1024, NRM_ONE_N = 16384;
+template <typename Val>
+__device__ __forceinline__ void nrm2_one(int64_t n, Val val, double *out, uint64_t *stamp)
+{
+#pragma clang fp contract(off)
+    constexpr int NW = NRM_ONE_NT / 64, NQ = NRM_ONE_N / 256 / NW;
+    __shared__ double part[NRM_ONE_N / 256];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    // the block sums' tree: t += t + 128, + 64, then + 32 .. + 1
+    auto tree = [&](const double (&e)[4]) {
+        double a = (e[0] + e[2]) + (e[1] + e[3]);
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) a += __shfl_down(a, w);
+        return a;
+    };
+    double e[NQ][4];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t i = (int64_t)(wv + q * NW) * 256 + lane + 64 * j;
+            const double v = i < n ? val(i) : 0.0;
+            e[q][j] = v * v;
+        }
+    const int m = (int)((n + 255) / 256);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (wv + q * NW >= m) break;
+        const double a = tree(e[q]);
+        if (lane == 0) part[wv + q * NW] = a;
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const double f[4] = {lane < m ? part[lane] : 0.0, 0.0, 0.0, 0.0};
+        const double a = tree(f);
+        if (lane == 0) {
+            out[0] = sqrt(a);
+            if (stamp) *stamp = __builtin_amdgcn_s_memrealtime();
+        }
+    }
+}
+
+template <typename V>
+__global__ __launch_bounds__(NRM_ONE_NT) void k_nrm2_one(int64_t n, const V *__restrict__ x,
+                                                         double *__restrict__ out,
+                                                         uint64_t *__restrict__ stamp)
+{
+    nrm2_one(n, [&](int64_t i) { return (double)x[i]; }, out, stamp);
+}
+
+// One refinement's start: b = I_d^s(-F/||F||) (tail [n, np) zeroed), r = b,
+// u = 0 and ||b||, in one launch (n <= NRM_ONE_N).
+__global__ __launch_bounds__(NRM_ONE_NT) void k_rhs_nrm2_one(int64_t n, int64_t np,
+                                                             const double *__restrict__ F,
+                                                             const double *__restrict__ fn,
+                                                             float *__restrict__ b,
+                                                             float *__restrict__ r,
+                                                             float *__restrict__ u,
+                                                             double *__restrict__ out,
+                                                             uint64_t *__restrict__ stamp)
+{
+    const double f = fn[0];
+    for (int64_t i = n + threadIdx.x; i < np; i += NRM_ONE_NT) b[i] = 0.0f;
+    nrm2_one(
+        n,
+        [&](int64_t i) {
+            const float v = (float)(-F[i] / f);
+            b[i] = v;
+            r[i] = v;
+            u[i] = 0.0f;
+            return (double)v;
+        },
+        out, stamp);
+}
 
 // ---------------------------------------------------------- vector kernels
 __global__ void k_fill_i32(int *p, int v, int64_t n)
@@ -549,17 +634,32 @@ __global__ void k_fill_f32(float *p, float v, int64_t n)
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }
-__global__ void k_iota_i32(int32_t *p, int64_t n)
+// The state of a factorisation attempt or of a solve in one launch: flags
+// cleared, identity interchanges (the pivoting path overwrites every entry if
+// it runs), publication or solve words cleared.
+__global__ void k_init_state(int nflags, int *flags, int64_t np, int32_t *ipiv, int64_t words,
+                              uint64_t *pub)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = (int32_t)i;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    if (t < nflags) flags[t] = 0;
+    for (int64_t i = t; i < np; i += step) ipiv[i] = (int32_t)i;
+    for (int64_t i = t; i < words; i += step) pub[i] = 0;
 }
-// b = I_d^s(-F/||F||), eq. (2.17); tail [n, np) zeroed
-__global__ void k_rhs_unit(int64_t n, int64_t np, const double *F, const double *fn, float *b)
+// b = I_d^s(-F/||F||), eq. (2.17); tail [n, np) zeroed; r = b and u = 0 with
+// r, u non-null
+__global__ void k_rhs_unit(int64_t n, int64_t np, const double *F, const double *fn, float *b,
+                           float *r, float *u)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = (float)(-F[i] / fn[0]);
-    else if (i < np) b[i] = 0.0f;
+    if (i < n) {
+        const float v = (float)(-F[i] / fn[0]);
+        b[i] = v;
+        if (r) r[i] = v;
+        if (u) u[i] = 0.0f;
+    } else if (i < np) {
+        b[i] = 0.0f;
+    }
 }
 // FP64 right-hand side -F/||F|| (Newton with a double-precision factorisation)
 __global__ void k_rhs_unit_f64(int64_t n, int64_t np, const double *F, const double *fn, double *b)
@@ -584,10 +684,14 @@ __global__ void k_newton_update_f64(int64_t n, double *x, const double *fn, cons
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) x[i] += fn[0] * u[i];
 }
-__global__ void k_axpy_f32(int64_t n, float *y, const float *x, float a)
+// uprev = u, u += d
+__global__ void k_ir_update(int64_t n, float *u, float *uprev, const float *d)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] += a * x[i];
+    if (i >= n) return;
+    const float v = u[i];
+    uprev[i] = v;
+    u[i] = v + d[i];
 }
 __global__ void k_vcopy_f32(int64_t n, float *d, const float *s)
 {
@@ -992,33 +1096,53 @@ hipError_t launch_copy_bytes(void *dst, const void *src, size_t bytes, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_nrm2_f64(int64_t n, const double *x, double *part, double *out, hipStream_t s)
+// `stamp` (optional): a timestamp taken once the norm is written
+template <typename V>
+static hipError_t nrm2_t(int64_t n, const V *x, double *part, double *out, uint64_t *stamp, hipStream_t s)
 {
-    const int nb = (int)std::min<int64_t>(NRM_BLOCKS, std::max<int64_t>(1, (n + 255) / 256));
-    hipLaunchKernelGGL(k_sumsq_part<double>, dim3(nb), dim3(256), 0, s, n, x, part);
-    hipLaunchKernelGGL(k_sum_sqrt, dim3(1), dim3(256), 0, s, nb, (const double *)part, out);
+    if (n <= NRM_ONE_N) {
+        hipLaunchKernelGGL(k_nrm2_one<V>, dim3(1), dim3(NRM_ONE_NT), 0, s, n, x, out, stamp);
+        return hipGetLastError();
+    }
+    const int nb = (int)std::min<int64_t>(NRM_BLOCKS, (n + 255) / 256);
+    hipLaunchKernelGGL(k_sumsq_part<V>, dim3(nb), dim3(256), 0, s, n, x, part);
+    hipLaunchKernelGGL(k_sum_sqrt, dim3(1), dim3(256), 0, s, nb, (const double *)part, out, stamp);
     return hipGetLastError();
 }
-
+hipError_t launch_nrm2_f64(int64_t n, const double *x, double *part, double *out, uint64_t *stamp,
+                           hipStream_t s)
+{
+    return nrm2_t(n, x, part, out, stamp, s);
+}
 hipError_t launch_nrm2_f32(int64_t n, const float *x, double *part, double *out, hipStream_t s)
 {
-    const int nb = (int)std::min<int64_t>(NRM_BLOCKS, std::max<int64_t>(1, (n + 255) / 256));
-    hipLaunchKernelGGL(k_sumsq_part<float>, dim3(nb), dim3(256), 0, s, n, x, part);
-    hipLaunchKernelGGL(k_sum_sqrt, dim3(1), dim3(256), 0, s, nb, (const double *)part, out);
-    return hipGetLastError();
+    return nrm2_t(n, x, part, out, nullptr, s);
+}
+hipError_t launch_rhs_start(int64_t n, int64_t np, const double *F, const double *fnorm, float *b,
+                            float *r, float *u, double *part, double *out, uint64_t *stamp, hipStream_t s)
+{
+    if (n <= NRM_ONE_N) {
+        hipLaunchKernelGGL(k_rhs_nrm2_one, dim3(1), dim3(NRM_ONE_NT), 0, s, n, np, F, fnorm, b, r, u,
+                           out, stamp);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_rhs_unit, dim3(nblk(np, 256)), dim3(256), 0, s, n, np, F, fnorm, b, r, u);
+    return nrm2_t(n, (const float *)b, part, out, stamp, s);
 }
 
 // A timestamp on the GPU timeline (the 100 MHz real-time counter), for the
-// report's per-phase times without host synchronisation: one lane of one
-// wavefront writes it (a vector store).
-__global__ __launch_bounds__(64) void k_stamp(uint64_t *p)
+// report's per-phase times without host synchronisation, into `count`
+// consecutive slots (the end of a phase is the start of the next): one
+// wavefront writes it (vector stores).
+__global__ __launch_bounds__(64) void k_stamp(uint64_t *p, int count)
 {
-    if (threadIdx.x == 0) *p = __builtin_amdgcn_s_memrealtime();
+    const uint64_t v = __builtin_amdgcn_s_memrealtime();
+    if ((int)threadIdx.x < count) p[threadIdx.x] = v;
 }
 
-hipError_t launch_stamp(uint64_t *p, hipStream_t s)
+hipError_t launch_stamp(uint64_t *p, int count, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_stamp, dim3(1), dim3(64), 0, s, p);
+    hipLaunchKernelGGL(k_stamp, dim3(1), dim3(64), 0, s, p, count);
     return hipGetLastError();
 }
 
@@ -1032,15 +1156,19 @@ hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s)
     hipLaunchKernelGGL(k_fill_f32, dim3(nblk(n, 256)), dim3(256), 0, s, p, v, n);
     return hipGetLastError();
 }
-hipError_t launch_iota_i32(int32_t *p, int64_t n, hipStream_t s)
+hipError_t launch_init_state(int nflags, int *flags, int64_t np, int32_t *ipiv, int64_t words,
+                              uint64_t *pub, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_iota_i32, dim3(nblk(n, 256)), dim3(256), 0, s, p, n);
+    const int64_t items = std::max<int64_t>({nflags, np, words});
+    const unsigned grid = (unsigned)std::min<int64_t>((items + 255) / 256, 1024);
+    hipLaunchKernelGGL(k_init_state, dim3(grid), dim3(256), 0, s, nflags, flags, np, ipiv, words, pub);
     return hipGetLastError();
 }
 hipError_t launch_rhs_unit(int64_t n, int64_t np, const double *F, const double *fnorm, float *b,
                            hipStream_t s)
 {
-    hipLaunchKernelGGL(k_rhs_unit, dim3(nblk(np, 256)), dim3(256), 0, s, n, np, F, fnorm, b);
+    hipLaunchKernelGGL(k_rhs_unit, dim3(nblk(np, 256)), dim3(256), 0, s, n, np, F, fnorm, b,
+                       (float *)nullptr, (float *)nullptr);
     return hipGetLastError();
 }
 hipError_t launch_rhs_unit_f64(int64_t n, int64_t np, const double *F, const double *fnorm,
@@ -1066,9 +1194,9 @@ hipError_t launch_newton_update_f64(int64_t n, double *x, const double *fnorm, c
     hipLaunchKernelGGL(k_newton_update_f64, dim3(nblk(n, 256)), dim3(256), 0, s, n, x, fnorm, u);
     return hipGetLastError();
 }
-hipError_t launch_axpy_f32(int64_t n, float *y, const float *x, float a, hipStream_t s)
+hipError_t launch_ir_update(int64_t n, float *u, float *uprev, const float *d, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_axpy_f32, dim3(nblk(n, 256)), dim3(256), 0, s, n, y, x, a);
+    hipLaunchKernelGGL(k_ir_update, dim3(nblk(n, 256)), dim3(256), 0, s, n, u, uprev, d);
     return hipGetLastError();
 }
 hipError_t launch_vcopy_f32(int64_t n, float *dst, const float *src, hipStream_t s)

@@ -575,12 +575,15 @@ __global__ __launch_bounds__(256) void k_trsv_lower(int64_t n, const T *__restri
 }
 
 // x = S U^{-1} y with S = diag(colscale) (null = identity); other blocks read
-// the unscaled solution (tagged).
+// the unscaled solution (tagged).  With u non-null the solution is a
+// refinement's correction and is added instead of stored: uprev = u, u += x
+// (two launches a sweep less).
 template <typename T, typename V, int BS>
 __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restrict__ LU, int64_t lda,
                                                     const V *__restrict__ yin,
                                                     const float *__restrict__ colscale,
-                                                    V *__restrict__ x, int *__restrict__ sync,
+                                                    V *__restrict__ x, V *__restrict__ u,
+                                                    V *__restrict__ uprev, int *__restrict__ sync,
                                                     uint32_t epoch, int *__restrict__ flags,
                                                     int round_out)
 {
@@ -592,7 +595,17 @@ __global__ __launch_bounds__(256) void k_trsv_upper(int64_t n, const T *__restri
     trsv_upper_block<T, V, BS>(
         sh, s_blk, nb, n, LU, lda, tag_words(sync), epoch, flags, round_out,
         [&](int64_t row) { return yin[row]; },
-        [&](int64_t row, V w) { x[row] = colscale ? w * (V)colscale[row] : w; });
+        [&](int64_t row, V w) {
+#pragma clang fp contract(off)
+            const V xi = colscale ? w * (V)colscale[row] : w;  // rounded before it is added
+            if (!u) {
+                x[row] = xi;
+                return;
+            }
+            const V ui = u[row];
+            uprev[row] = ui;
+            u[row] = ui + xi;
+        });
 }
 
 // ticket (4 ints, keeps the tag words 16-byte aligned) + 2 tag words per entry
@@ -612,11 +625,11 @@ static hipError_t trsv_lower_t(int64_t n, const void *LU, int64_t lda, const int
 template <typename T, typename V>
 static hipError_t trsv_upper_t(int64_t n, const void *LU, int64_t lda, const V *y,
                                const float *colscale, V *x, int *sync, uint32_t epoch, int *flags,
-                               hipStream_t s, int round_out = 0)
+                               hipStream_t s, int round_out = 0, V *u = nullptr, V *uprev = nullptr)
 {
     const unsigned nb = (unsigned)((n + TRSV_BS - 1) / TRSV_BS);
     hipLaunchKernelGGL((k_trsv_upper<T, V, TRSV_BS>), dim3(nb), dim3(256), 0, s, n, (const T *)LU,
-                       lda, y, colscale, x, sync, epoch, flags, round_out);
+                       lda, y, colscale, x, u, uprev, sync, epoch, flags, round_out);
     return hipGetLastError();
 }
 
@@ -635,13 +648,13 @@ hipError_t launch_trsv_lower(int prec, int64_t n, const void *LU, int64_t lda, c
 
 hipError_t launch_trsv_upper(int prec, int64_t n, const void *LU, int64_t lda, const float *y,
                              const float *colscale, float *x, int *sync, uint32_t epoch, int *flags,
-                             hipStream_t s, int round_out)
+                             hipStream_t s, int round_out, float *u, float *uprev)
 {
     switch (prec) {
-    case N3P_FP16: return trsv_upper_t<f16, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out);
-    case N3P_BF16: return trsv_upper_t<bf16, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out);
-    case N3P_FP32: return trsv_upper_t<float, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out);
-    case N3P_FP64: return trsv_upper_t<double, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out);
+    case N3P_FP16: return trsv_upper_t<f16, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out, u, uprev);
+    case N3P_BF16: return trsv_upper_t<bf16, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out, u, uprev);
+    case N3P_FP32: return trsv_upper_t<float, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out, u, uprev);
+    case N3P_FP64: return trsv_upper_t<double, float>(n, LU, lda, y, colscale, x, sync, epoch, flags, s, round_out, u, uprev);
     }
     return hipErrorInvalidValue;
 }

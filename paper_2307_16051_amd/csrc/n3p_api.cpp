@@ -65,6 +65,13 @@ bool valid_prec(int p) { return p >= N3P_FP16 && p <= N3P_FP64; }
 int64_t padded(int64_t n) { return round_up(std::max<int64_t>(n, 1), NB_PAD); }
 
 // ------------------------------------------------------------ factor state
+// What the host reads back: one copy and one wait fetch all of it.
+struct DevState {
+    int flags[NFLAGS];
+    double fn;   // ||F||
+    double nrm;  // the linear solver's last norm
+};
+
 struct FactorWs {
     int prec = 0;
     int64_t Np = 0;
@@ -77,7 +84,8 @@ struct FactorWs {
     void *xch = nullptr;      // pivoting path: exchange words and interchange list
     int32_t *ipiv = nullptr;  // Np
     int32_t *perm = nullptr;  // Np (device), valid if pivoted
-    int *flags = nullptr;     // NFLAGS
+    DevState *state = nullptr;  // flags, and the norms read back with them
+    int *flags = nullptr;       // state->flags
     uint64_t *pub = nullptr;  // FP16/BF16: publication words of the diagonal-square kernel
     float *inv = nullptr;     // FP16/BF16: the leaves' triangular inverses
 };
@@ -96,7 +104,7 @@ size_t factor_bytes(int prec, int64_t n, Bump &b, FactorWs *f, char *base)
     size_t oS = b.take(pivot_xch_bytes(prec, Np));
     size_t oI = b.take((size_t)Np * 4);
     size_t oP = b.take((size_t)Np * 4);
-    size_t oF = b.take((size_t)NFLAGS * 4);
+    size_t oF = b.take(sizeof(DevState));
     size_t oPub = top_path(prec) ? b.take(top_pub_words() * 8) : 0;
     size_t oInv = top_path(prec) ? b.take(top_inv_floats() * 4) : 0;
     if (f && base) {
@@ -111,7 +119,8 @@ size_t factor_bytes(int prec, int64_t n, Bump &b, FactorWs *f, char *base)
         f->xch = base + oS;
         f->ipiv = (int32_t *)(base + oI);
         f->perm = (int32_t *)(base + oP);
-        f->flags = (int *)(base + oF);
+        f->state = (DevState *)(base + oF);
+        f->flags = f->state->flags;
     }
     return b.off;
 }
@@ -123,9 +132,9 @@ struct FactorResult {
     bool timeout = false;
 };
 
-int read_flags(const FactorWs &f, hipStream_t s, int *h)
+int read_state(const FactorWs &f, hipStream_t s, DevState *h)
 {
-    HIPCHK(hipMemcpyAsync(h, f.flags, NFLAGS * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(h, f.state, sizeof(DevState), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     return 0;
 }
@@ -189,7 +198,7 @@ int getrf_spec(const FactorWs &f, hipStream_t s)
 // the update of block j + 1's square, then that square factored in the same
 // launch as the rest of block j's update (the rows below the square included).  LT alternates between
 // two buffers by block parity.  Publication tags are unique within a
-// factorisation (the area is cleared once at its start).
+// factorisation (launch_init_state clears the area).
 // The last square ends with the last leaf that holds a column of the matrix
 // (20 us a leaf: n = 256 took eight leaves for four).  Up to two squares there
 // is no 256 x 256 update, so everything else ends there too; beyond, the
@@ -202,7 +211,6 @@ int getrf_spec_top(const FactorWs &f, hipStream_t s)
     char *A = (char *)f.A;
     char *LTb[2] = {(char *)f.LT, (char *)f.LT + (size_t)f.Np * NB_OUT * es};
     auto at = [&](int64_t i, int64_t j) { return (void *)(A + ((size_t)i + (size_t)j * lda) * es); };
-    HIPCHK(launch_fill_i32((int *)f.pub, 0, (int64_t)(top_pub_words() * 2), s));
     uint32_t tag0 = 1;
     HIPCHK(launch_top(prec, 0, (int)std::min<int64_t>(NB_OUT, nf), f.A, lda, LTb[0], f.pub, f.inv,
                       f.flags, tag0, s));
@@ -338,22 +346,21 @@ int getrf_pivot(const FactorWs &f, hipStream_t s)
 }
 
 // Factor f.A in place.  `refill` restores the unfactored matrix into f.A
-// (needed when the no-interchange attempt is abandoned).  `xdev` (optional):
-// one double copied to *xhost in the same host wait as the flags (work the
-// caller queued before the factorisation).
+// (needed when the no-interchange attempt is abandoned).  `nrm` (optional):
+// takes f.state->nrm, fetched with the flags (a norm the caller queued before
+// the factorisation).
 template <typename Refill>
 int getrf_run(const FactorWs &f, hipStream_t s, Refill refill, FactorResult *res,
-              const double *xdev = nullptr, double *xhost = nullptr)
+              double *nrm = nullptr)
 {
-    int h[NFLAGS];
-    HIPCHK(launch_fill_i32(f.flags, 0, NFLAGS, s));
+    DevState hs;
+    const int *h = hs.flags;
+    HIPCHK(launch_init_state(NFLAGS, f.flags, f.Np, f.ipiv,
+                              top_path(f.prec) ? (int64_t)top_pub_words() : 0, f.pub, s));
     if (top_path(f.prec)) CHK(getrf_spec_top(f, s));
     else CHK(getrf_spec(f, s));
-    // identity interchanges, queued before the wait (the pivoting path
-    // overwrites every entry if it runs)
-    HIPCHK(launch_iota_i32(f.ipiv, f.Np, s));
-    if (xdev) HIPCHK(hipMemcpyAsync(xhost, xdev, sizeof(double), hipMemcpyDeviceToHost, s));
-    CHK(read_flags(f, s, h));
+    CHK(read_state(f, s, &hs));
+    if (nrm) *nrm = hs.nrm;
     res->pivoted = false;
     if (h[FLAG_FAIL]) {
         // the pivoting path holds one row per thread in at most PIVOT_MAX_WG
@@ -367,7 +374,7 @@ int getrf_run(const FactorWs &f, hipStream_t s, Refill refill, FactorResult *res
         CHK(refill());
         HIPCHK(launch_fill_i32(f.flags, 0, NFLAGS, s));
         CHK(getrf_pivot(f, s));
-        CHK(read_flags(f, s, h));
+        CHK(read_state(f, s, &hs));
         res->pivoted = true;
         // permutation vector for the triangular solves: perm[k] = original row at position k
         std::vector<int32_t> ip((size_t)f.Np), pm((size_t)f.Np);
@@ -395,7 +402,7 @@ struct SolveWs {
     FactorWs f;
     float *J = nullptr;        // n x n FP32 (ld n)
     float *colscale = nullptr; // Np
-    double *F = nullptr, *D = nullptr, *h = nullptr, *part = nullptr, *scal = nullptr;
+    double *F = nullptr, *D = nullptr, *h = nullptr, *part = nullptr;
     size_t part_len = 0;
     float *b = nullptr, *u = nullptr, *uprev = nullptr, *r = nullptr, *d = nullptr, *y = nullptr,
           *xs = nullptr, *z = nullptr, *av = nullptr, *w = nullptr, *V = nullptr;
@@ -431,7 +438,6 @@ size_t solve_layout(int64_t n, int prec, int ls, int m, int fftmode, SolveWs *w,
     size_t oF = b.take((size_t)n * 8), oD = b.take((size_t)n * 8), oH = b.take((size_t)2 * n * 8);
     const size_t pl = part_len_for(n);
     size_t oP = b.take(pl * 8);
-    size_t oS = b.take(64 * 8);
     size_t vec = (size_t)Np * 4;
     size_t ob = b.take(vec), ou = b.take(vec), oup = b.take(vec), orr = b.take(vec), od = b.take(vec),
            oy = b.take(vec), oxs = b.take(vec), oz = b.take(vec), oav = b.take(vec), ow = b.take(vec);
@@ -483,7 +489,6 @@ size_t solve_layout(int64_t n, int prec, int ls, int m, int fftmode, SolveWs *w,
         w->h = (double *)(base + oH);
         w->part = (double *)(base + oP);
         w->part_len = pl;
-        w->scal = (double *)(base + oS);
         w->stamps = (uint64_t *)(base + ostamp);
         w->b = (float *)(base + ob);
         w->u = (float *)(base + ou);
@@ -576,13 +581,14 @@ int lin_matvec(LinCtx &c, const float *v, float *y)
     return 0;
 }
 
-// out = S U^{-1} L^{-1} P in   (the preconditioner-vector product)
-int apply_prec(LinCtx &c, const float *in, float *out)
+// out = S U^{-1} L^{-1} P in   (the preconditioner-vector product); with u
+// non-null it is added: uprev = u, u += the product
+int apply_prec(LinCtx &c, const float *in, float *out, float *u = nullptr, float *uprev = nullptr)
 {
     HIPCHK(launch_trsv_lower(c.prec, c.n, c.LU, c.ldlu, c.perm, in, c.y, c.sync, c.epoch->next(),
                              c.flags, c.s));
     HIPCHK(launch_trsv_upper(c.prec, c.n, c.LU, c.ldlu, c.y, c.colscale, out, c.sync,
-                             c.epoch->next(), c.flags, c.s));
+                             c.epoch->next(), c.flags, c.s, 0, u, uprev));
     return 0;
 }
 
@@ -707,13 +713,16 @@ int refine(LinCtx &c, const float *b, float *u, double tol, int max_sweeps, bool
             int its = 0;
             CHK(gmres_lp(c, c.r, c.d, m, gtol, max_restarts, &its));
             o->inner += its;
+            HIPCHK(launch_ir_update(c.n, u, c.uprev, c.d, c.s));
         } else {
-            if (c.ir_half && rn > 0.0) CHK(apply_prec_half(c, c.r, rn, c.d));
-            else CHK(apply_prec(c, c.r, c.d));
+            if (c.ir_half && rn > 0.0) {
+                CHK(apply_prec_half(c, c.r, rn, c.d));
+                HIPCHK(launch_ir_update(c.n, u, c.uprev, c.d, c.s));
+            } else {
+                CHK(apply_prec(c, c.r, nullptr, u, c.uprev));
+            }
             o->inner += 1;
         }
-        HIPCHK(launch_vcopy_f32(c.n, c.uprev, u, c.s));
-        HIPCHK(launch_axpy_f32(c.n, u, c.d, 1.0f, c.s));
         CHK(lin_resid(c, u, b, c.r, c.part));
         double rnew = 0.0;
         CHK(norm32(c, c.r, &rnew));
@@ -826,7 +835,9 @@ N3P_API size_t n3p_workspace_size(int64_t n, int lu_prec, int ls, const n3p_opti
     return solve_layout(n, lu_prec, ls, opt_m(opt), fft_mode(opt), nullptr, nullptr);
 }
 
-static int eval_residual(const n3p_problem *p, const SolveWs &w, const double *x, hipStream_t s)
+// F(x) and, in w.f.state->fn, ||F||; `stamp` (optional): a timestamp at the end
+static int eval_residual(const n3p_problem *p, const SolveWs &w, const double *x, uint64_t *stamp,
+                         hipStream_t s)
 {
     switch (p->kind) {
     case 0:
@@ -841,7 +852,7 @@ static int eval_residual(const n3p_problem *p, const SolveWs &w, const double *x
         break;
     default: return N3P_E_INVALID;
     }
-    HIPCHK(launch_nrm2_f64(w.n, w.F, w.part, w.scal, s));
+    HIPCHK(launch_nrm2_f64(w.n, w.F, w.part, &w.f.state->fn, stamp, s));
     return 0;
 }
 
@@ -902,16 +913,29 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
     // once when the solve ends
     int tslot = 0;
     std::vector<std::pair<int, float *>> tpairs;
+    // the slots of the running phase's start and end, for a kernel that stamps
+    // them itself (null: no timing, or no slots left)
+    auto start_slot = [&]() -> uint64_t * {
+        return opt.timing && tslot + 2 <= NSTAMPS ? w.stamps + tslot : nullptr;
+    };
+    auto stop_slot = [&](float *acc) -> uint64_t * {
+        uint64_t *p0 = start_slot();
+        if (!p0) return nullptr;
+        tpairs.emplace_back(tslot, acc);
+        tslot += 2;
+        return p0 + 1;
+    };
     auto tstart = [&]() -> int {
-        if (opt.timing && tslot + 2 <= NSTAMPS) HIPCHK(launch_stamp(w.stamps + tslot, s));
+        if (uint64_t *q = start_slot()) HIPCHK(launch_stamp(q, 1, s));
         return 0;
     };
     auto tstop = [&](float *acc) -> int {
-        if (opt.timing && tslot + 2 <= NSTAMPS) {
-            HIPCHK(launch_stamp(w.stamps + tslot + 1, s));
-            tpairs.emplace_back(tslot, acc);
-            tslot += 2;
-        }
+        if (uint64_t *q = stop_slot(acc)) HIPCHK(launch_stamp(q, 1, s));
+        return 0;
+    };
+    // the end of a phase and the start of the next, in neighbouring slots
+    auto tnext = [&](float *acc) -> int {
+        if (uint64_t *q = stop_slot(acc)) HIPCHK(launch_stamp(q, start_slot() ? 2 : 1, s));
         return 0;
     };
     // the two events bracketing the solve; the guard destroys them on every
@@ -931,8 +955,8 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
     HIPCHK(hipEventRecord(ev.a, s));
 
     Epoch epoch;
-    HIPCHK(launch_fill_i32(w.sync, 0, (int64_t)trsv_sync_ints(w.Np), s));
-    HIPCHK(launch_fill_i32(w.f.flags, 0, NFLAGS, s));
+    HIPCHK(launch_init_state(NFLAGS, w.f.flags, 0, nullptr, (int64_t)trsv_sync_ints(w.Np) / 2,
+                             (uint64_t *)w.sync, s));
     if (p->kind == 0) HIPCHK(launch_hinv(n, w.h, s));
     if (w.L) HIPCHK(launch_hk_setup(n, w.L, w.tw, w.Hh, w.t1, w.t2, s));
 
@@ -940,11 +964,10 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
     double fn = 0.0;
     CHK(tstart());
     {
-        int st = eval_residual(p, w, x, s);
+        int st = eval_residual(p, w, x, stop_slot(&t_resid), s);
         if (st) return st;
     }
-    CHK(d2h_double(w.scal, &fn, s));
-    CHK(tstop(&t_resid));
+    CHK(d2h_double(&w.f.state->fn, &fn, s));
     if (!std::isfinite(fn)) return N3P_E_NONFINITE;
     const double f0 = fn;
     const double tau = opt.tau_abs_override >= 0 ? opt.tau_abs_override : opt.tau_r * fn + opt.tau_a;
@@ -974,7 +997,7 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
     lc.d = w.d;
     lc.uprev = w.uprev;
     lc.part = w.part;
-    lc.scal = w.scal + 1;
+    lc.scal = &w.f.state->nrm;
     lc.H = w.H;
     lc.ydev = w.ydev;
     lc.sync = w.sync;
@@ -1007,19 +1030,16 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
     while (fn > tau && its < opt.maxit) {
         double nb_pre = 0.0;
         if (pre_rhs) {
-            HIPCHK(launch_rhs_unit(n, w.Np, w.F, w.scal, w.b, s));
-            HIPCHK(launch_nrm2_f32(n, w.b, w.part, lc.scal, s));
-            HIPCHK(launch_fill_f32(w.u, 0.0f, n, s));
-            HIPCHK(launch_vcopy_f32(n, lc.r, w.b, s));
+            HIPCHK(launch_rhs_start(n, w.Np, w.F, &w.f.state->fn, w.b, lc.r, w.u, w.part, lc.scal,
+                                    start_slot(), s));
         }
         // --- J = F'(x) stored FP32, J_h = I_s^h(J) (column scaled for FP16)
         bool scaled = want_scale;
         FactorResult fr;
         for (int attempt = 0; attempt < 2; ++attempt) {
-            CHK(tstart());
+            if (attempt > 0 || !pre_rhs) CHK(tstart());
             CHK(build_jacobian(p, w, x, tl, scaled, s));
-            CHK(tstop(&t_jac));
-            CHK(tstart());
+            CHK(tnext(&t_jac));
             auto refill = [&]() -> int {
                 if (want_scale && scaled && tl > 3.0f) tl -= 6.0f;
                 // the FP64 factorisation of a built-in problem takes the FP64
@@ -1030,8 +1050,8 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
                                           scaled ? w.colscale : nullptr, tl, w.f.flags, s));
                 return 0;
             };
-            CHK(getrf_run(w.f, s, refill, &fr, pre_rhs ? lc.scal : nullptr, &nb_pre));
-            CHK(tstop(&t_getrf));
+            CHK(getrf_run(w.f, s, refill, &fr, pre_rhs ? &nb_pre : nullptr));
+            CHK(tnext(&t_getrf));
             if (fr.timeout) return N3P_E_TIMEOUT;
             if (fr.nonfinite && want_scale && attempt == 0 && tl > 3.0f) {
                 tl -= 6.0f;  // retry with the column targets 2^6 lower
@@ -1045,9 +1065,8 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
         lc.colscale = (fp16 && scaled) ? w.colscale : nullptr;
 
         // --- step: J u = -F/||F|| (eq. (2.17)); s = ||F|| u (eq. (2.18))
-        CHK(tstart());
         LinOut lo;
-        const double *fnd = w.scal;  // device ||F||
+        const double *fnd = &w.f.state->fn;  // device ||F||
         if (lu_prec == N3P_FP64 && ls == N3P_DIRECT) {
             // Newton with a double-precision factorisation: one FP64 solve
             HIPCHK(launch_rhs_unit_f64(n, w.Np, w.F, fnd, w.b64, s));
@@ -1075,20 +1094,21 @@ N3P_API int n3p_solve(const n3p_problem *p, double *x, int lu_prec, int ls,
             }
             HIPCHK(launch_newton_update_f32(n, x, fnd, w.u, s));
         }
-        CHK(tstop(&t_solve));
-        {
-            int h[NFLAGS];
-            CHK(read_flags(w.f, s, h));
-            if (h[FLAG_TIMEOUT]) return N3P_E_TIMEOUT;
+        // --- F(x); a bounded wait of the solves that expired is seen in the
+        // same read, but before a callback is handed the x it left
+        CHK(tnext(&t_solve));
+        DevState h;
+        if (p->kind == 2) {
+            CHK(read_state(w.f, s, &h));
+            if (h.flags[FLAG_TIMEOUT]) return N3P_E_TIMEOUT;
         }
-        // --- F(x)
-        CHK(tstart());
         {
-            int st = eval_residual(p, w, x, s);
+            int st = eval_residual(p, w, x, stop_slot(&t_resid), s);
             if (st) return st;
         }
-        CHK(d2h_double(w.scal, &fn, s));
-        CHK(tstop(&t_resid));
+        CHK(read_state(w.f, s, &h));
+        if (h.flags[FLAG_TIMEOUT]) return N3P_E_TIMEOUT;
+        fn = h.fn;
         if (rep) {
             rep->lin_its[its] = ls == N3P_GMRES_IR ? lo.inner : lo.sweeps;
             rep->lin_outer[its] = lo.sweeps;
@@ -1205,8 +1225,8 @@ N3P_API int n3p_getrs(int prec, int64_t n, const void *LU, int64_t lda, const in
         std::swap(pm[k], pm[ip[k]]);
     }
     HIPCHK(hipMemcpyAsync(f.perm, pm.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(launch_fill_i32(sync, 0, (int64_t)trsv_sync_ints(padded(n)), s));
-    HIPCHK(launch_fill_i32(f.flags, 0, NFLAGS, s));
+    HIPCHK(launch_init_state(NFLAGS, f.flags, 0, nullptr, (int64_t)trsv_sync_ints(padded(n)) / 2,
+                             (uint64_t *)sync, s));
     const size_t vs = prec == N3P_FP64 ? 8 : 4;
     HIPCHK(hipMemcpyAsync(bc, b, (size_t)n * vs, hipMemcpyDeviceToDevice, s));
     if (prec == N3P_FP64) {
@@ -1220,9 +1240,9 @@ N3P_API int n3p_getrs(int prec, int64_t n, const void *LU, int64_t lda, const in
         HIPCHK(launch_trsv_upper(prec, n, LU, lda, (const float *)y, nullptr, (float *)b, sync, 2,
                                  f.flags, s));
     }
-    int h[NFLAGS];
-    CHK(read_flags(f, s, h));
-    if (h[FLAG_TIMEOUT]) return N3P_E_TIMEOUT;
+    DevState h;
+    CHK(read_state(f, s, &h));
+    if (h.flags[FLAG_TIMEOUT]) return N3P_E_TIMEOUT;
     return N3P_OK;
 }
 
@@ -1276,8 +1296,8 @@ static int lin_common(int prec, int64_t n, const float *A, int64_t lda, const vo
     char *base = (char *)(((uintptr_t)ws + ALIGN - 1) / ALIGN * ALIGN);
     int32_t *perm_buf = nullptr;
     lin_layout(n, m, base, c, &perm_buf);
-    HIPCHK(launch_fill_i32(c->sync, 0, (int64_t)trsv_sync_ints(padded(n)), s));
-    HIPCHK(launch_fill_i32(c->flags, 0, NFLAGS, s));
+    HIPCHK(launch_init_state(NFLAGS, c->flags, 0, nullptr, (int64_t)trsv_sync_ints(padded(n)) / 2,
+                             (uint64_t *)c->sync, s));
     c->perm = nullptr;
     if (ipiv) {
         std::vector<int32_t> ip((size_t)n), pm((size_t)n);

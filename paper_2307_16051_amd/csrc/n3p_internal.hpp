@@ -172,14 +172,20 @@ hipError_t launch_pad_copy_out(int prec, int64_t n, int64_t Np, const void *Ap, 
 hipError_t launch_copy_bytes(void *dst, const void *src, size_t bytes, hipStream_t s);
 
 // reductions and vector kernels
-hipError_t launch_nrm2_f64(int64_t n, const double *x, double *part, double *out, hipStream_t s);
+hipError_t launch_nrm2_f64(int64_t n, const double *x, double *part, double *out, uint64_t *stamp,
+                           hipStream_t s);
 hipError_t launch_nrm2_f32(int64_t n, const float *x, double *part, double *out, hipStream_t s);
 hipError_t launch_fill_i32(int *p, int v, int64_t n, hipStream_t s);
-// GPU-timeline timestamp (100 MHz real-time counter ticks) into *p
-hipError_t launch_stamp(uint64_t *p, hipStream_t s);
+// GPU-timeline timestamp (100 MHz real-time counter ticks) into p[0 .. count)
+hipError_t launch_stamp(uint64_t *p, int count, hipStream_t s);
 constexpr double STAMP_MS_PER_TICK = 1e-5;
 hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s);
-hipError_t launch_iota_i32(int32_t *p, int64_t n, hipStream_t s);
+hipError_t launch_init_state(int nflags, int *flags, int64_t np, int32_t *ipiv, int64_t words,
+                              uint64_t *pub, hipStream_t s);
+// b = I_d^s(-F/||F||) (tail [n, np) zeroed), r = b, u = 0, *out = ||b||
+hipError_t launch_rhs_start(int64_t n, int64_t np, const double *F, const double *fnorm, float *b,
+                            float *r, float *u, double *part, double *out, uint64_t *stamp,
+                            hipStream_t s);
 // b = -F / ||F|| (FP64 in, FP32 out, padded tail zeroed up to np)
 hipError_t launch_rhs_unit(int64_t n, int64_t np, const double *F, const double *fnorm, float *b,
                            hipStream_t s);
@@ -192,7 +198,7 @@ hipError_t launch_newton_update_f32(int64_t n, double *x, const double *fnorm, c
                                     hipStream_t s);
 hipError_t launch_newton_update_f64(int64_t n, double *x, const double *fnorm, const double *u,
                                     hipStream_t s);
-hipError_t launch_axpy_f32(int64_t n, float *y, const float *x, float a, hipStream_t s);
+hipError_t launch_ir_update(int64_t n, float *u, float *uprev, const float *d, hipStream_t s);
 hipError_t launch_vcopy_f32(int64_t n, float *dst, const float *src, hipStream_t s);
 hipError_t launch_f32_to_f64(int64_t n, const float *src, double *dst, hipStream_t s);
 hipError_t launch_f64_to_f32(int64_t n, const double *src, float *dst, hipStream_t s);
@@ -255,7 +261,8 @@ hipError_t launch_trsv_lower(int prec, int64_t n, const void *LU, int64_t lda, c
                              hipStream_t s, int round_out = 0);
 hipError_t launch_trsv_upper(int prec, int64_t n, const void *LU, int64_t lda, const float *y,
                              const float *colscale, float *x, int *sync, uint32_t epoch, int *flags,
-                             hipStream_t s, int round_out = 0);
+                             hipStream_t s, int round_out = 0, float *u = nullptr,
+                             float *uprev = nullptr);
 // out = in * a rounded to the factor type of prec (held as FP32)
 hipError_t launch_scale_round(int prec, int64_t n, const float *in, float a, float *out, hipStream_t s);
 hipError_t launch_trsv_lower_f64(int64_t n, const double *LU, int64_t lda, const int32_t *perm,

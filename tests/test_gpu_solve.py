@@ -170,3 +170,25 @@ def test_callback_problem_matches_builtin(env):
     x2, rep2 = n3p.solve_heq(n, c)
     assert rep.its == rep2.its
     assert rel_err(x.cpu().numpy(), x2.cpu().numpy()) < 1e-12
+
+
+@pytest.mark.parametrize("n", [1, 63, 255, 256, 257, 4097, 16383, 16384, 16385])
+def test_residual_norm_chunk_edges(env, n):
+    """||F(x0)|| against the norm of F(x0) in extended precision: chunks of 256
+    elements, one workgroup up to 16384.  At most 8 additions within a chunk
+    and 8 over the chunks, a product and a root: below 18 roundings of the sum
+    of squares, half of them in its root."""
+    n3p, torch = env
+    print("case residual norm n=%d" % n, flush=True)
+    x0 = torch.ones(n, dtype=torch.float64, device="cuda")
+    F, _ = n3p.heq_residual(x0, 0.9)
+    Fh = F.cpu().numpy().astype(np.longdouble)
+    ref = float(np.sqrt(np.sum(Fh * Fh)))
+    opts = n3p.Options.default()
+    opts.maxit = 0
+    _, rep = n3p.solve_heq(n, 0.9, x=x0.clone(), opts=opts)
+    assert rep.its == 0
+    assert abs(rep.f0 - ref) <= 10 * 2.0 ** -53 * ref
+    if n <= 4097:
+        _, full = n3p.solve_heq(n, 0.9)
+        assert full.status == 0 and full.f0 == rep.f0
