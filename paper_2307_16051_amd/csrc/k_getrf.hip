@@ -506,7 +506,7 @@ static hipError_t gemm16_t(int64_t M, int64_t N, int64_t K, const void *At, int6
                            const void *B, int64_t ldb, void *C, int64_t ldc, int *flags, bool ca,
                            hipStream_t s)
 {
-    if (M % 64 || N % 64 || K % 32) return hipErrorInvalidValue;
+    if (M % 64 || N % 64 || K % 64) return hipErrorInvalidValue;
     if (M % 256 == 0 && N % 256 == 0 && M * N >= (int64_t)256 * 256 * 128)
         gemm16_go<T, 256, 256, 2, 4, 32>(M, N, K, At, ldat, B, ldb, C, ldc, flags, ca, s);
     else if (M % 128 == 0 && N % 128 == 0 && M * N >= (int64_t)128 * 128 * 128)
