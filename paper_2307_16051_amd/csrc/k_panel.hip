@@ -255,20 +255,6 @@ __device__ __forceinline__ float wave_max(float v)
     return fmaxf(fmaxf(a, b), fmaxf(c, d));
 }
 
-// max over a block of NW wavefronts
-template <int NW>
-__device__ __forceinline__ float block_max(float v, float *red)
-{
-    v = wave_max(v);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float m = red[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) m = fmaxf(m, red[i]);
-    __syncthreads();
-    return m;
-}
-
 typedef float DmRow[PT + 1];
 
 // Triangular inverses in place in Dm: U^{-1} on and above the diagonal,
@@ -1036,6 +1022,10 @@ __device__ __forceinline__ int six(int k, int c, int R)
 // I + 1's sum are requested as soon as step I's sum has consumed its
 // registers, so their latency overlaps step I's diagonal-block work; waves
 // 0..3 then solve the block (one fragment each).
+// A block is a chain of four barriers (halves joined, largest entry, staged
+// operands, block stored); with the inverse's operands requested by all eight
+// waves at the head of the block, and six barriers, 256 workgroups took 74 us
+// instead of 70 (4.4 us a block) and 480 (two rounds) 159 instead of 150.
 constexpr int TRSM_PF = 2 * (NB_OUT / PT - 1);  // 16-deep K steps of the longest half sum
 
 template <typename T> struct TrsmCtx {
@@ -1044,8 +1034,8 @@ template <typename T> struct TrsmCtx {
     T *A;
     const T *LT, *inv;
     int ex[32];              // the leaves' exponents (s of U^{-1}, s of L^{-1})
-    T *buf, *stg;
-    float *pbuf, *red;
+    T *buf, *sth, *stl;      // the tile; the staged high and low parts of one block
+    float *pbuf;             // the K halves' hand-over, 16 x 64 values per fragment
     bool bad, fail;
 };
 
@@ -1053,14 +1043,20 @@ template <typename T> struct TrsmCtx {
 // entries, waves 0..3) staged for use as a matrix-core operand; returns the
 // exponent
 template <typename T>
-__device__ __forceinline__ int stage_split(TrsmCtx<T> &c, const float (&y)[16], bool rowmajor, int blk)
+__device__ __forceinline__ int stage_split(TrsmCtx<T> &c, const float (&y)[16], bool rowmajor)
 {
     float mx = 0.0f;
 #pragma unroll
     for (int q = 0; q < 16; ++q) mx = fmaxf(mx, fabsf(y[q]));
-    const int sy = scale_exp(block_max<8>(c.w < 4 ? mx : 0.0f, c.red));
+    // the four maxima cross through the head of each wavefront's own part of
+    // pbuf, which it has read and which is written again only after the next
+    // block's first barrier
+    mx = wave_max(mx);
+    if (c.w < 4 && (threadIdx.x & 63) == 0) c.pbuf[c.w * 1024] = mx;
+    __syncthreads();
+    if (c.w >= 4) return 0;
+    const int sy = scale_exp(fmaxf(fmaxf(c.pbuf[0], c.pbuf[1024]), fmaxf(c.pbuf[2048], c.pbuf[3072])));
     const float fy = ldexpf(1.0f, sy);
-    if (c.w >= 4) return sy;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         T hi[4], lo[4];
@@ -1078,12 +1074,12 @@ __device__ __forceinline__ int stage_split(TrsmCtx<T> &c, const float (&y)[16], 
         const int k = 32 * c.fm + 8 * g + 4 * c.h;  // fragment row (block-local)
         if (rowmajor) {  // role L: entry (tile row i, leaf column k)
             const int i = 32 * c.fn + c.l32;
-            *(u32x2 *)&c.buf[tix(i, 64 * blk + k, c.W)] = sh;
-            *(u32x2 *)&c.stg[tix(i, k, PT)] = sl;
+            *(u32x2 *)&c.sth[tix(i, k, PT)] = sh;
+            *(u32x2 *)&c.stl[tix(i, k, PT)] = sl;
         } else {         // role U: entry (block row k, slab column cc)
             const int cc = 32 * c.fn + c.l32;
-            *(u32x2 *)&c.buf[six(64 * blk + k, cc, c.W)] = sh;
-            *(u32x2 *)&c.stg[six(k, cc, PT)] = sl;
+            *(u32x2 *)&c.sth[six(k, cc, PT)] = sh;
+            *(u32x2 *)&c.stl[six(k, cc, PT)] = sl;
         }
     }
     return sy;
@@ -1127,19 +1123,23 @@ template <typename T, int I> struct StepL {
         if (I >= c.nl) return;
         const int W = c.W, h = c.h, l32 = c.l32, fm = c.fm, fn = c.fn;
         const int i = 32 * fn + l32;
-        const T *iv = c.inv + (size_t)I * IH_LEAF + (fm * 4 * 64 + 32 * h + l32) * 8;
-        u32x4 uh[4], ul[4];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            uh[ks] = *(const u32x4 *)(iv + IH_UHI + ks * 64 * 8);
-            ul[ks] = *(const u32x4 *)(iv + IH_ULO + ks * 64 * 8);
-        }
         // this wave's half of P^T = U(<I, I)^T L(:, <I)^T
         f32x16 p = zero16();
 #pragma unroll
         for (int s = 0; s < 2 * I; ++s) {
             const vec bv = as_vec<T>(*(const u32x4 *)&c.buf[tix(i, c.kh * 32 * I + 16 * s + 8 * h, W)]);
             p = pmma<T>::op(as_vec<T>(pf[s]), bv, p);
+        }
+        // the inverse's operands (waves 0..3), then the next block's: in this
+        // order, so that the wait for these does not wait for those
+        u32x4 uh[4], ul[4];
+        if (c.w < 4) {
+            const T *iv = c.inv + (size_t)I * IH_LEAF + (fm * 4 * 64 + 32 * h + l32) * 8;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                uh[ks] = *(const u32x4 *)(iv + IH_UHI + ks * 64 * 8);
+                ul[ks] = *(const u32x4 *)(iv + IH_ULO + ks * 64 * 8);
+            }
         }
         StepL<T, I + 1>::prefetch(c, pf);
         join_halves(c, p);
@@ -1152,20 +1152,19 @@ template <typename T, int I> struct StepL {
             for (int q = 0; q < 4; ++q)
                 y[4 * g + q] = to_f32(from_bits<T>(xv[q >> 1] >> (16 * (q & 1)))) - p[4 * g + q];
         }
-        const int sy = stage_split<T>(c, y, true, I);
+        const int sy = stage_split<T>(c, y, true);
         __syncthreads();
         f32x16 r = zero16();
         if (c.w < 4) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const vec yh = as_vec<T>(*(const u32x4 *)&c.buf[tix(i, 64 * I + 16 * ks + 8 * h, W)]);
-                const vec yl = as_vec<T>(*(const u32x4 *)&c.stg[tix(i, 16 * ks + 8 * h, PT)]);
+                const vec yh = as_vec<T>(*(const u32x4 *)&c.sth[tix(i, 16 * ks + 8 * h, PT)]);
+                const vec yl = as_vec<T>(*(const u32x4 *)&c.stl[tix(i, 16 * ks + 8 * h, PT)]);
                 r = pmma<T>::op(as_vec<T>(uh[ks]), yh, r);
                 r = pmma<T>::op(as_vec<T>(ul[ks]), yh, r);
                 r = pmma<T>::op(as_vec<T>(uh[ks]), yl, r);
             }
         }
-        __syncthreads();  // staged reads done before L overwrites them
         if (c.w < 4) {
             const float back = ldexpf(1.0f, -(c.ex[2 * I] + sy));
             const float margin = 1.0f - 1.0f / 256.0f;
@@ -1218,19 +1217,23 @@ template <typename T, int I> struct StepU {
         u32x2 xa[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) xa[g] = *(const u32x2 *)(acol + 8 * g + 4 * h);
-        const T *iv = c.inv + (size_t)I * IH_LEAF + (fm * 4 * 64 + 32 * h + l32) * 8;
-        u32x4 lh[4], ll[4];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            lh[ks] = *(const u32x4 *)(iv + IH_LHI + ks * 64 * 8);
-            ll[ks] = *(const u32x4 *)(iv + IH_LLO + ks * 64 * 8);
-        }
         // this wave's half of P = L(I, <I) U(<I)
         f32x16 p = zero16();
 #pragma unroll
         for (int s = 0; s < 2 * I; ++s) {
             const vec bv = as_vec<T>(*(const u32x4 *)&c.buf[six(c.kh * 32 * I + 16 * s + 8 * h, cc, W)]);
             p = pmma<T>::op(as_vec<T>(pf[s]), bv, p);
+        }
+        // the inverse's operands (waves 0..3), then the next block's: in this
+        // order, so that the wait for these does not wait for those
+        u32x4 lh[4], ll[4];
+        if (c.w < 4) {
+            const T *iv = c.inv + (size_t)I * IH_LEAF + (fm * 4 * 64 + 32 * h + l32) * 8;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                lh[ks] = *(const u32x4 *)(iv + IH_LHI + ks * 64 * 8);
+                ll[ks] = *(const u32x4 *)(iv + IH_LLO + ks * 64 * 8);
+            }
         }
         StepU<T, I + 1>::prefetch(c, pf);
         join_halves(c, p);
@@ -1241,20 +1244,19 @@ template <typename T, int I> struct StepU {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 z[4 * g + q] = to_f32(from_bits<T>(xa[g][q >> 1] >> (16 * (q & 1)))) - p[4 * g + q];
-        const int sz = stage_split<T>(c, z, false, I);
+        const int sz = stage_split<T>(c, z, false);
         __syncthreads();
         f32x16 r = zero16();
         if (c.w < 4) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const vec zh = as_vec<T>(*(const u32x4 *)&c.buf[six(64 * I + 16 * ks + 8 * h, cc, W)]);
-                const vec zl = as_vec<T>(*(const u32x4 *)&c.stg[six(16 * ks + 8 * h, cc, PT)]);
+                const vec zh = as_vec<T>(*(const u32x4 *)&c.sth[six(16 * ks + 8 * h, cc, PT)]);
+                const vec zl = as_vec<T>(*(const u32x4 *)&c.stl[six(16 * ks + 8 * h, cc, PT)]);
                 r = pmma<T>::op(as_vec<T>(lh[ks]), zh, r);
                 r = pmma<T>::op(as_vec<T>(ll[ks]), zh, r);
                 r = pmma<T>::op(as_vec<T>(lh[ks]), zl, r);
             }
         }
-        __syncthreads();
         if (c.w < 4) {
             const float back = ldexpf(1.0f, -(c.ex[2 * I + 1] + sz));
 #pragma unroll
@@ -1285,11 +1287,13 @@ template <typename T>
 __global__ __launch_bounds__(TRSM_THREADS) void k_trsm(TrsmArgs a)
 {
     __shared__ __attribute__((aligned(16))) T buf[PT * NB_OUT];
-    __shared__ __attribute__((aligned(16))) T stg[PT * PT];
-    __shared__ float pbuf[4 * 16 * 64];
-    __shared__ float red[8];
-    if (block_flag(&a.flags[FLAG_FAIL])) return;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    __shared__ __attribute__((aligned(16))) T sth[PT * PT], stl[PT * PT];
+    __shared__ float pbuf[4 * 16 * 64];  // with the above all of the 160 KB
+    if (threadIdx.x == 0) pbuf[0] = __int_as_float(ld_flag(&a.flags[FLAG_FAIL]));
+    __syncthreads();
+    if (__float_as_int(pbuf[0])) return;  // block-uniform
+    __syncthreads();
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int W = a.W;
     const int64_t k0 = a.k0, kend = k0 + W, lda = a.lda;
     T *A = (T *)a.A;
@@ -1308,9 +1312,9 @@ __global__ __launch_bounds__(TRSM_THREADS) void k_trsm(TrsmArgs a)
     c.LT = (const T *)a.LT;
     c.inv = (const T *)a.inv;
     c.buf = buf;
-    c.stg = stg;
+    c.sth = sth;
+    c.stl = stl;
     c.pbuf = pbuf;
-    c.red = red;
     c.bad = false;
     c.fail = false;
     {
@@ -1404,7 +1408,7 @@ hipError_t launch_top_gemm(int prec, int64_t k0, int W, void *A, int64_t lda, vo
                            const void *At2, const void *B2, void *C2, hipStream_t s)
 {
     if (W < PT || W > NB_OUT || W % PT || lda % 8 || k0 % PT) return hipErrorInvalidValue;
-    if (M <= 0 || N <= 0 || M % 256 || N % 256 || K % 32 || K <= 0) return hipErrorInvalidValue;
+    if (M <= 0 || N <= 0 || M % 256 || N % 256 || K % 64 || K <= 0) return hipErrorInvalidValue;
     if (M2 < 0 || N2 < 0 || M2 % 256 || N2 % 256) return hipErrorInvalidValue;
     if (M2 == 0 || N2 == 0) M2 = N2 = 0;
     TopGemmArgs g{TopArgs{k0, W, A, lda, LT, pub, inv, flags, tag0}, W / PT, (int)M, (int)N, (int)K,
