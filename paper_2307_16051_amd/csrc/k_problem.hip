@@ -545,9 +545,10 @@ constexpr int NRM_BLOCKS = 256;
 // The same norm by one workgroup, n <= NRM_ONE_N: a wavefront takes a chunk of
 // 256 elements (four loads a lane, up to four chunks in flight) and adds it in
 // the order of the block sums above, so the result is the same to the last
-// bit.  val(i) gives element i < n.  A launch instead of two, 3 us at n = 1000
-// and 4 us at n = 16384 against 4 + 4 us and the gap between them; beyond,
-// one workgroup's loads bound it (256 KiB take longer than the second launch).
+// bit.  val(i) gives element i < n.  A launch instead of two: 3 us at n = 256,
+// 3-5 us at n = 1000 and 8.3 us at n = 16384, against 1.8 + 1.8, 4 + 3 and 4.2 +
+// 4.8 us and a gap of about 4 us between them; beyond 16384 one workgroup's
+// loads (eight bytes times n at 64 B a cycle) outgrow the second launch.
 constexpr int NRM_ONE_NT = 1024, NRM_ONE_N = 16384;
 template <typename Val>
 __device__ __forceinline__ void nrm2_one(int64_t n, Val val, double *out, uint64_t *stamp)
