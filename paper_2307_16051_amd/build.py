@@ -16,6 +16,10 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libn3p.so")
 SOURCES = ["k_problem.hip", "k_getrf.hip", "k_panel.hip", "k_pivot.hip", "k_solve.hip", "k_fft.hip", "k_bench.hip", "n3p_api.cpp", "n3p_batch.cpp"]
 ARCH = "gfx950"
+# the tests' entry points to single launches, linked with these objects
+PANELS_SRC = os.path.join(ROOT, "tests", "native", "panels.cpp")
+PANELS_LIB = os.path.join(ROOT, "tests", "native", "libpanels.so")
+PANELS_OBJECTS = ["k_problem.hip", "k_pivot.hip"]
 
 
 def hipcc() -> str:
@@ -68,6 +72,18 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_panels(verbose: bool = False) -> str:
+    """tests/native/libpanels.so, from the kernel objects of the last build()."""
+    objs = [os.path.join(BUILD, src + ".o") for src in PANELS_OBJECTS] + [_compile(PANELS_SRC, verbose)]
+    tmp = PANELS_LIB + ".tmp"
+    cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp] + objs
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, PANELS_LIB)
+    return PANELS_LIB
+
+
 def build_host_sanitized(out_dir: str, verbose: bool = False) -> str:
     """A copy of the library whose host driver code (HOST_SOURCES) is built
     with HOST_SANITIZE, linked with the kernel objects of the last build().
@@ -93,4 +109,5 @@ def build_host_sanitized(out_dir: str, verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     build(verbose="-v" in sys.argv)
+    build_panels(verbose="-v" in sys.argv)
     print(LIB)

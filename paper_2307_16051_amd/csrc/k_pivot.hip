@@ -51,6 +51,10 @@ namespace n3p {
 constexpr int PC_SPIN_LIMIT = 1 << 20;         // polls of ~1 us: a wait that long has failed
 constexpr int PC_LIST_INTS = 1 + 4 * NB_LEAF;  // count + 128 (dest, src) pairs
 constexpr int PC_NLIST = NB_OUT / NB_LEAF;     // one list per leaf of an outer block
+// The count of a list whose leaf found an expired wait of an earlier one and
+// left: it has no interchanges and no panel, and the kernels behind it, which
+// index by both, leave the matrix as it is.
+constexpr int PC_ABANDONED = -1;
 
 template <typename CT> struct pc_cfg;
 // rows per thread, words per value, threads per workgroup
@@ -793,10 +797,16 @@ __global__ __launch_bounds__(PO_NT) void k_pivot_one(int64_t Np, int64_t c0, con
     __shared__ int pivs[L], prow[L];  // column k: the pivot's position, and its row
     __shared__ int moves;
     if (threadIdx.x == 0) moves = 0;
-    if (block_flag(&flags[FLAG_TIMEOUT])) return;
     const PoScratch<CT> sc(scratch);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = (int)(Np - c0);
+    if (block_flag(&flags[FLAG_TIMEOUT])) {
+        // abandoned (see PC_ABANDONED); the pivots' rows stay valid indices
+        for (int i = tid; i < m; i += PO_NT) sc.pos[i] = -1;
+        if (tid < L) sc.prow[tid] = tid;
+        if (tid == 0) list[0] = PC_ABANDONED;
+        return;
+    }
     int row[R], pos[R];
     CT v[R][SW];
     uint64_t zero = 0;  // columns with a zero pivot: no multipliers, no update
@@ -1014,7 +1024,7 @@ __global__ __launch_bounds__(PO_NT) void k_pivot_one(int64_t Np, int64_t c0, con
 
 // Rows [64 tile, 64 tile + 64) of a panel that k_pivot_one factored, from its
 // scratch into A by position, and those below the leaf into LT (through LDS:
-// a row of LT is contiguous).
+// a row of LT is contiguous).  An abandoned panel has no positions.
 template <typename T, typename CT>
 __device__ __forceinline__ void store_panel(const PoScratch<CT> &sc, int tile, T *__restrict__ A,
                                             int64_t lda, T *__restrict__ LT, int64_t c0, int64_t k0,
@@ -1028,8 +1038,10 @@ __device__ __forceinline__ void store_panel(const PoScratch<CT> &sc, int tile, T
     for (int i = 0; i < L / 4; ++i) {
         const int k = wv + 4 * i;
         const T x = to_store_d<T>((double)sc.at(k, row));
-        bad |= !isfinite(to_f32(x));  // the stored value (FP16 overflows above 65504)
-        A[(c0 + pos) + (c0 + k) * lda] = x;
+        if (pos >= 0) {
+            bad |= !isfinite(to_f32(x));  // the stored value (FP16 overflows above 65504)
+            A[(c0 + pos) + (c0 + k) * lda] = x;
+        }
         buf[lane][k] = x;
     }
     if (bad) set_flag(&flags[FLAG_NONFINITE], 1);
@@ -1215,6 +1227,7 @@ __global__ __launch_bounds__(256) void k_gather_u12(T *__restrict__ A, int64_t l
     } else {
         load_l11<T, CT>(A, lda, c0, Lm);
     }
+    if (n == PC_ABANDONED) return;  // the same word for every thread
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h)
