@@ -595,6 +595,7 @@ __global__ __launch_bounds__(pc_cfg<CT>::TH) void k_pivot_coop(int64_t Np, int64
                                                            int32_t *__restrict__ ipiv,
                                                            T *__restrict__ LT,
                                                            uint64_t *__restrict__ xch, int pmax,
+                                                           int *__restrict__ list,
                                                            int *__restrict__ flags)
 {
     typedef PcState<T, CT> S;
@@ -607,7 +608,10 @@ __global__ __launch_bounds__(pc_cfg<CT>::TH) void k_pivot_coop(int64_t Np, int64
     __shared__ __attribute__((aligned(16))) CT krw[NWV][L];
     __shared__ __attribute__((aligned(16))) CT crow[NWV][L];
     __shared__ int pivs[L];
-    if (block_flag(&flags[FLAG_TIMEOUT])) return;
+    if (block_flag(&flags[FLAG_TIMEOUT])) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) list[0] = PC_ABANDONED;
+        return;
+    }
     S st;
     st.tid = threadIdx.x;
     st.lane = st.tid & 63;
@@ -637,7 +641,6 @@ __global__ __launch_bounds__(pc_cfg<CT>::TH) void k_pivot_coop(int64_t Np, int64
     st.pivs = pivs;
     st.dead = false;
     st.nonfin = false;
-    int *list = (int *)(st.dummy + (size_t)pmax * NWV * L * W) + ((c0 - k0) / L) * PC_LIST_INTS;
     const int tid = st.tid, lane = st.lane, wv = st.wv, wg = st.wg, m = st.m;
 
     st.rowi = wg * RW + tid;
@@ -1073,7 +1076,7 @@ __global__ __launch_bounds__(1024) void k_compose_lists(const int *__restrict__ 
     __syncthreads();
     for (int l = 0; l < nl; ++l) {
         const int *list = lists + l * PC_LIST_INTS;
-        const int c = list[0];
+        const int c = list[0];  // PC_ABANDONED: none
         int d = 0;
         unsigned short v = 0;
         if (t < c) {
@@ -1324,11 +1327,11 @@ hipError_t launch_pivot_reset(int prec, int64_t Np, void *xch, hipStream_t s)
 
 template <typename T, typename CT>
 static hipError_t pivot_coop_t(int64_t Np, int64_t c0, int64_t k0, void *A, int64_t lda,
-                               int32_t *ipiv, void *LT, void *xch, int pmax, int P, int *flags,
-                               hipStream_t s)
+                               int32_t *ipiv, void *LT, void *xch, int pmax, int P, int *list,
+                               int *flags, hipStream_t s)
 {
     hipLaunchKernelGGL((k_pivot_coop<T, CT>), dim3(P), dim3(pc_cfg<CT>::TH), 0, s, Np, c0, k0, (T *)A,
-                       lda, ipiv, (T *)LT, (uint64_t *)xch, pmax, flags);
+                       lda, ipiv, (T *)LT, (uint64_t *)xch, pmax, list, flags);
     return hipGetLastError();
 }
 
@@ -1357,9 +1360,9 @@ hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void 
     const int64_t rw = pc_rows_per_wg(prec), m = Np - c0;
     const int64_t P = (m + rw - 1) / rw, pmax = pc_pmax(prec, Np);
     if (m < NB_LEAF || m % NB_LEAF || P > PIVOT_MAX_WG) return hipErrorInvalidValue;
+    int *list = const_cast<int *>(pc_lists(prec, Np, xch)) + ((c0 - k0) / NB_LEAF) * PC_LIST_INTS;
     if (m <= PO_MAX_ROWS) {
         void *sc = po_scratch(prec, Np, xch);
-        int *list = const_cast<int *>(pc_lists(prec, Np, xch)) + ((c0 - k0) / NB_LEAF) * PC_LIST_INTS;
         switch (prec) {
         case N3P_FP16: return pivot_one_t<f16, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
         case N3P_BF16: return pivot_one_t<bf16, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
@@ -1369,10 +1372,10 @@ hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void 
         return hipErrorInvalidValue;
     }
     switch (prec) {
-    case N3P_FP16: return pivot_coop_t<f16, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, flags, s);
-    case N3P_BF16: return pivot_coop_t<bf16, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, flags, s);
-    case N3P_FP32: return pivot_coop_t<float, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, flags, s);
-    case N3P_FP64: return pivot_coop_t<double, double>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, flags, s);
+    case N3P_FP16: return pivot_coop_t<f16, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, list, flags, s);
+    case N3P_BF16: return pivot_coop_t<bf16, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, list, flags, s);
+    case N3P_FP32: return pivot_coop_t<float, float>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, list, flags, s);
+    case N3P_FP64: return pivot_coop_t<double, double>(Np, c0, k0, A, lda, ipiv, LT, xch, (int)pmax, (int)P, list, flags, s);
     }
     return hipErrorInvalidValue;
 }

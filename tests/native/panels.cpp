@@ -22,4 +22,10 @@ N3P_API int panels_leaf(int prec, int64_t Np, int64_t c0, int64_t k0, int64_t ke
     return (int)e;
 }
 
+N3P_API int panels_block(int prec, int64_t Np, int64_t k0, int64_t kend, void *A, int64_t lda,
+                         void *xch, void *stream)
+{
+    return (int)launch_gather_block(prec, Np, k0, kend, A, lda, xch, (hipStream_t)stream);
+}
+
 }  // extern "C"

@@ -28,6 +28,7 @@ def env():
     lib.panels_xch_bytes.argtypes = [ctypes.c_int, ctypes.c_int64]
     i64, vp = ctypes.c_int64, ctypes.c_void_p
     lib.panels_leaf.argtypes = [ctypes.c_int, i64, i64, i64, i64, vp, i64, vp, vp, vp, vp, vp]
+    lib.panels_block.argtypes = [ctypes.c_int, i64, i64, i64, vp, i64, vp, vp]
     return lib, torch
 
 
@@ -57,6 +58,11 @@ class Panel:
                                  self.flags.data_ptr(), self.torch.cuda.current_stream().cuda_stream)
         assert e == 0
 
+    def block(self, k0, kend):
+        e = self.lib.panels_block(self.prec, self.Np, k0, kend, self.A.data_ptr(), self.lda,
+                                  self.xch.data_ptr(), self.torch.cuda.current_stream().cuda_stream)
+        assert e == 0
+
     def assert_untouched(self):
         self.torch.cuda.synchronize()
         for name, a, b in zip(("A", "LT", "ipiv", "flags"), self.before, self.state()):
@@ -71,4 +77,31 @@ def test_one_workgroup_leaf_after_an_expired_wait(env, prec, Np, c0, k0):
     print("case abandoned leaf prec %d Np=%d c0=%d" % (prec, Np, c0), flush=True)
     p = Panel(lib, torch, prec, Np, Np + 8)
     p.leaf(c0, k0, min(k0 + lib.panels_block_columns(), Np))
+    p.assert_untouched()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_cooperative_leaf_after_an_expired_wait(env, prec):
+    """More than 4096 rows below the leaf: a panel over several workgroups,
+    with the interchanges of an earlier outer block still in its list."""
+    lib, torch = env
+    Np, c0 = 5248, 1024
+    print("case abandoned cooperative leaf prec %d" % prec, flush=True)
+    p = Panel(lib, torch, prec, Np, c0 - 8)
+    p.leaf(c0, c0, c0 + lib.panels_block_columns())
+    p.assert_untouched()
+
+
+@pytest.mark.parametrize("Np", [2112, 5248])
+def test_block_interchanges_after_an_expired_wait(env, Np):
+    """The lists of an outer block whose leaves were all abandoned hold the
+    rows of the block before, above its own: none of them may be applied."""
+    lib, torch = env
+    k0 = lib.panels_block_columns()
+    kend = 2 * k0
+    print("case abandoned block Np=%d" % Np, flush=True)
+    p = Panel(lib, torch, 0, Np, k0 - 8)
+    for c0 in range(k0, kend, 64):
+        p.leaf(c0, k0, kend)
+    p.block(k0, kend)
     p.assert_untouched()
