@@ -983,7 +983,18 @@ hipError_t launch_krylov_update(int64_t n, const float *V, int64_t ldv, int k, c
 // uprev = u, u += d, with the stored half-precision factors promoted to FP32
 // as they are read (Section 2.3); LOWER, then upper, one launch each.
 //
-// The row blocks are those of the single solves.  A fixed grid takes them by
+// Two forms by the request's size (never by what else is in the batch):
+//
+// At most B_SUBST_NP rows: one workgroup substitutes (b_substitute, in the
+// lower launch).  A wavefront takes the diagonal block, a row a lane, while the
+// other three hold the block's columns of the rows that it updates, so B_SUBST_NP
+// is four wavefronts' rows.  With at most four blocks the chain is shorter than
+// the inverses, tickets, hand-offs and second launch of the other form: 64
+// requests of 200 rows 26 us a call against 48, of 64 rows 10 against 18.  At 512
+// rows the other form is ahead (51 us for 32 requests, against 68 by one
+// workgroup of sixteen wavefronts a request).
+//
+// More rows: the row blocks of the single solves.  A fixed grid takes them by
 // ticket, all slots' first blocks, then all second ones, and so on: a block
 // waits only on blocks of its own slot with smaller tickets, which running
 // workgroups hold, so the waits end whatever the grid.  The published words
@@ -994,6 +1005,74 @@ hipError_t launch_krylov_update(int64_t n, const float *V, int64_t ldv, int k, c
 // CU: 347 us a call for 32 requests of 128 to 2048 rows, now 101 for the two
 // launches (240 for one workgroup with the substitution of a block beside the
 // update by the one before it).
+template <typename T>
+__device__ __forceinline__ void b_substitute(const BDesc &q, float (&y)[B_SUBST_NP])
+{
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int n = (int)q.n, Np = (int)q.Np;
+    const T *__restrict__ A = (const T *)q.A;
+    // one row of the 64 columns from b0, requested a block ahead
+    T c[64], cn[64], dn;
+    auto fetch = [&](int b0, int row) {
+        const T *src = A + std::min(row, Np - 1) + (int64_t)b0 * Np;
+#pragma unroll
+        for (int k = 0; k < 64; ++k) cn[k] = src[(int64_t)k * Np];
+        dn = A[(int64_t)(b0 + lane) * (Np + 1)];
+    };
+    auto update = [&](int b0, int row) {
+        float acc = y[row];
+#pragma unroll
+        for (int k = 0; k < 64; ++k) acc -= to_f32(c[k]) * y[b0 + k];
+        y[row] = acc;
+    };
+    y[t] = t < Np ? q.r[t] : 0.0f;
+    fetch(0, t);
+    __syncthreads();
+#pragma unroll 1
+    for (int b0 = 0; b0 < Np; b0 += 64) {  // forward, unit lower
+#pragma unroll
+        for (int k = 0; k < 64; ++k) c[k] = cn[k];
+        // then the last block's upper half and the rows above it
+        if (b0 + 64 < Np) fetch(b0 + 64, b0 + 64 + t);
+        else fetch(b0, wv == 0 ? b0 + t : t - 64);
+        if (wv == 0) {
+            float yi = y[b0 + lane];
+#pragma unroll
+            for (int k = 0; k < 64; ++k) yi -= (lane > k ? to_f32(c[k]) : 0.0f) * lane_bcast(yi, k);
+            y[b0 + lane] = yi;
+        }
+        __syncthreads();
+        if (wv > 0 && b0 + t < Np) update(b0, b0 + t);
+        __syncthreads();
+    }
+#pragma unroll 1
+    for (int b0 = Np - 64; b0 >= 0; b0 -= 64) {  // backward, upper
+        const T d = dn;
+#pragma unroll
+        for (int k = 0; k < 64; ++k) c[k] = cn[k];
+        if (b0 > 0) fetch(b0 - 64, wv == 0 ? b0 - 64 + t : t - 64);
+        if (wv == 0) {
+            const float rd = 1.0f / to_f32(d);
+            float yi = y[b0 + lane];
+#pragma unroll
+            for (int k = 63; k >= 0; --k) {
+                if (lane == k) yi *= rd;
+                yi -= (lane < k ? to_f32(c[k]) : 0.0f) * lane_bcast(yi, k);
+            }
+            y[b0 + lane] = yi;
+        }
+        __syncthreads();
+        if (wv > 0 && t - 64 < b0) update(b0, t - 64);
+        __syncthreads();
+    }
+    if (t < Np) {
+        const float di = t < n ? (q.colscale ? y[t] * q.colscale[t] : y[t]) : 0.0f;
+        const float ui = q.u[t];
+        q.uprev[t] = ui;
+        q.u[t] = ui + di;
+    }
+}
+
 template <typename T, bool LOWER>
 __global__ __launch_bounds__(256) void k_b_trsv(const BDesc *__restrict__ d,
                                                 const BState *__restrict__ st, int nslots,
@@ -1003,16 +1082,23 @@ __global__ __launch_bounds__(256) void k_b_trsv(const BDesc *__restrict__ d,
     static_assert(B_MAX_SLOTS <= 256 && NLEV <= 256, "one thread per slot and per level");
     __shared__ TrsvLds<float, BS> sh;
     __shared__ int nbs[B_MAX_SLOTS], order[B_MAX_SLOTS], lev[NLEV + 1], s_item;
+    __shared__ float y_one[B_SUBST_NP];
     const int t = threadIdx.x;
-    // blocks per slot, the slots by falling number of blocks, and the number
+    // blocks per slot (of the requests solved by blocks), the slots by falling number of blocks, and the number
     // of items on the levels before each
     int nb = 0;
     if (t < nslots) {
         const int on = st[t].ir_on != 0, nl = b_factor_leaves(d[t], st[t]);
         nb = on * nl * (NB_LEAF / BS);
+        if (nb <= B_SUBST_NP / BS) nb = 0;
         nbs[t] = nb;
     }
-    __syncthreads();
+    if constexpr (LOWER) {
+        const int s = blockIdx.x;
+        if (s < nslots && d[s].Np <= B_SUBST_NP && st[s].ir_on && b_factor_leaves(d[s], st[s]))
+            b_substitute<T>(d[s], y_one);
+    }
+    if (!__syncthreads_or(nb)) return;
     int rank = 0, cnt = 0;
     for (int j = 0; j < nslots; ++j) {
         const int o = nbs[j];
@@ -1090,20 +1176,24 @@ __global__ __launch_bounds__(MV_NT) void k_b_gemv(const BDesc *__restrict__ d,
 
 // two workgroups fit a CU (256 registers a lane, 53 KB of LDS)
 constexpr unsigned B_TRSV_GRID = 512;
+static_assert(B_TRSV_GRID >= B_MAX_SLOTS, "a workgroup for every small request");
 template <typename T>
-static hipError_t b_solve_t(const BDesc *d, const BState *st, int nslots, int *tickets, hipStream_t s)
+static hipError_t b_solve_t(const BDesc *d, const BState *st, int nslots, bool blocks, int *tickets,
+                            hipStream_t s)
 {
-    hipLaunchKernelGGL((k_b_trsv<T, true>), dim3(B_TRSV_GRID), dim3(256), 0, s, d, st, nslots, tickets);
-    hipLaunchKernelGGL((k_b_trsv<T, false>), dim3(B_TRSV_GRID), dim3(256), 0, s, d, st, nslots, tickets + 1);
+    const dim3 grid(blocks ? B_TRSV_GRID : (unsigned)nslots);
+    hipLaunchKernelGGL((k_b_trsv<T, true>), grid, dim3(256), 0, s, d, st, nslots, tickets);
+    if (blocks)
+        hipLaunchKernelGGL((k_b_trsv<T, false>), grid, dim3(256), 0, s, d, st, nslots, tickets + 1);
     return hipGetLastError();
 }
 
-hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots, int *tickets,
-                          hipStream_t s)
+hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots, bool blocks,
+                          int *tickets, hipStream_t s)
 {
     switch (prec) {
-    case N3P_FP16: return b_solve_t<f16>(d, st, nslots, tickets, s);
-    case N3P_BF16: return b_solve_t<bf16>(d, st, nslots, tickets, s);
+    case N3P_FP16: return b_solve_t<f16>(d, st, nslots, blocks, tickets, s);
+    case N3P_BF16: return b_solve_t<bf16>(d, st, nslots, blocks, tickets, s);
     }
     return hipErrorInvalidValue;
 }

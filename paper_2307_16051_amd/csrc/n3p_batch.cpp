@@ -169,7 +169,8 @@ struct n3p_engine {
     Pool alloc;
     size_t req_base = 0;                        // first pool byte usable by requests
     std::map<int, hipGraphExec_t> g_factor;     // keyed by the number of leaves
-    hipGraphExec_t g_sweep = nullptr, g_final = nullptr;
+    hipGraphExec_t g_sweep[2] = {nullptr, nullptr};  // by whether a request is solved by blocks
+    hipGraphExec_t g_final = nullptr;
     bool any_fresh = false;
 
     int nslots() const { return cfg.max_slots; }
@@ -185,9 +186,10 @@ struct n3p_engine {
         BHIP(launch_b_ir_init(d_desc, d_state, nslots(), prm, s));
         return 0;
     }
-    int seq_sweep()
+    // blocks: a request of more than B_SUBST_NP rows may be refining
+    int seq_sweep(bool blocks)
     {
-        BHIP(launch_b_solve(cfg.lu_prec, d_desc, d_state, nslots(), d_tickets, s));
+        BHIP(launch_b_solve(cfg.lu_prec, d_desc, d_state, nslots(), blocks, d_tickets, s));
         BHIP(launch_b_gemv(d_desc, d_state, nslots(), cfg.vec_grid, s));
         BHIP(launch_b_ir_check(d_desc, d_state, nslots(), prm, d_tickets, s));
         return 0;
@@ -226,11 +228,12 @@ struct n3p_engine {
         BHIP(hipGraphLaunch(it->second, s));
         return 0;
     }
-    int run_sweep()
+    int run_sweep(bool blocks)
     {
-        if (!cfg.use_graphs) return seq_sweep();
-        if (!g_sweep) BCHK(capture(&g_sweep, [&] { return seq_sweep(); }));
-        BHIP(hipGraphLaunch(g_sweep, s));
+        if (!cfg.use_graphs) return seq_sweep(blocks);
+        hipGraphExec_t &g = g_sweep[blocks];
+        if (!g) BCHK(capture(&g, [&] { return seq_sweep(blocks); }));
+        BHIP(hipGraphLaunch(g, s));
         return 0;
     }
     int run_final()
@@ -269,15 +272,16 @@ struct n3p_engine {
                 leaves = std::max(leaves, slot_np[k] / B_LEAF);
         if (leaves > 0) {
             BCHK(run_factor(leaves));
+            const bool blocks = leaves * B_LEAF > B_SUBST_NP;
             // two sweeps cover most steps; then sweep while any slot is still refining
-            BCHK(run_sweep());
-            BCHK(run_sweep());
+            BCHK(run_sweep(blocks));
+            BCHK(run_sweep(blocks));
             for (int sw = 2; sw < prm.max_sweeps; ++sw) {
                 BCHK(pull_states());
                 bool on = false;
                 for (int k = 0; k < nslots(); ++k) on |= hstate[k].phase == BP_RUN && hstate[k].ir_on;
                 if (!on) break;
-                BCHK(run_sweep());
+                BCHK(run_sweep(blocks));
             }
             BCHK(run_final());
         }
@@ -344,7 +348,8 @@ struct n3p_engine {
     ~n3p_engine()
     {
         for (auto &kv : g_factor) (void)hipGraphExecDestroy(kv.second);
-        if (g_sweep) (void)hipGraphExecDestroy(g_sweep);
+        for (hipGraphExec_t g : g_sweep)
+            if (g) (void)hipGraphExecDestroy(g);
         if (g_final) (void)hipGraphExecDestroy(g_final);
         if (s) (void)hipStreamDestroy(s);
     }

@@ -311,6 +311,7 @@ hipError_t launch_hk_jv(int64_t n, int64_t np, int L, double c, const double *D,
 constexpr int B_LEAF = NB_LEAF;      // leaf width and padding granule (64)
 constexpr int B_MAX_NP = 4096;       // largest padded size of a batched solve
 constexpr int B_TICKETS = 2;         // block tickets of the lower and the upper solve
+constexpr int B_SUBST_NP = 256;      // most padded rows that one workgroup solves by substitution
 
 constexpr int B_MAX_SLOTS = 256;
 
@@ -405,9 +406,10 @@ hipError_t launch_b_leaf(int prec, const BDesc *d, const BState *st, int nslots,
 hipError_t launch_b_gemm(int prec, const BDesc *d, const BState *st, int nslots, int leaf,
                          int kc, int grid, hipStream_t s);
 hipError_t launch_b_ir_init(const BDesc *d, BState *st, int nslots, BParams p, hipStream_t s);
-// tickets: B_TICKETS ints, zero before each sweep (k_b_ir_check clears them)
-hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots, int *tickets,
-                          hipStream_t s);
+// blocks: slots of more than B_SUBST_NP rows may be refining; tickets: B_TICKETS
+// ints, zero before each sweep (k_b_ir_check clears them)
+hipError_t launch_b_solve(int prec, const BDesc *d, const BState *st, int nslots, bool blocks,
+                          int *tickets, hipStream_t s);
 hipError_t launch_b_gemv(const BDesc *d, const BState *st, int nslots, int grid, hipStream_t s);
 hipError_t launch_b_ir_check(const BDesc *d, BState *st, int nslots, BParams p, int *tickets,
                              hipStream_t s);

@@ -222,3 +222,34 @@ def test_engine_more_slots_than_a_wavefront(env, count):
         assert rep.status == 0 and rep.its in (its_ref, its_ref + 1), (s, n, c)
         assert rel_err(x.cpu().numpy(), xr) <= 1e-9, (s, n, c)
     eng.close()
+
+
+@pytest.mark.parametrize("prec", ["FP16", "BF16"])
+def test_engine_small_requests_alone_and_beside_large_ones(env, prec):
+    """Requests of up to 256 padded rows are solved by substitution, larger
+    ones by blocks: sizes on both sides of the line and at the blocks' edges,
+    first all small ones together (no launch for blocks), then beside requests
+    of more rows, with the same bits."""
+    n3p, torch = env
+    p = getattr(n3p, prec)
+    small = [(1, 0.9), (2, 0.5), (63, 0.9), (64, 0.99), (65, 0.9), (128, 0.99), (129, 0.5),
+             (192, 0.9), (193, 0.99), (255, 0.9), (256, 0.99)]
+    large = [(257, 0.9), (320, 0.99), (1000, 0.9)]
+    print("case engine small requests %s" % prec, flush=True)
+    xs = {}
+    for reqs in (small, large, small + large):
+        cfg = n3p.EngineConfig.default(max_slots=16, max_n=1024, lu_prec=p)
+        eng = n3p.Engine(make_pool(n3p, torch, [n for n, _ in reqs], 16, p), cfg)
+        slots = [eng.admit(n, c) for n, c in reqs]
+        assert None not in slots
+        run_to_completion(eng, slots)
+        for (n, c), s in zip(reqs, slots):
+            x = torch.empty(n, dtype=torch.float64, device="cuda")
+            rep = eng.collect(s, x)
+            xr, its_ref = oracle_ref(n, c)
+            assert rep.status == 0 and rep.its in (its_ref, its_ref + 1), (n, c)
+            assert rel_err(x.cpu().numpy(), xr) <= 1e-9, (n, c)
+            if n in xs:
+                assert torch.equal(x, xs[n]), (n, c)
+            xs[n] = x
+        eng.close()
