@@ -719,17 +719,24 @@ __global__ __launch_bounds__(pc_cfg<CT>::TH) void k_pivot_coop(int64_t Np, int64
 // set the time (0.42 us per earlier column and sub-panel), and past 4096 the
 // registers end, which is where the line to k_pivot_coop lies.
 constexpr int PO_MAX_ROWS = 4096, PO_NT = 512;
+// rows per thread for a panel of m rows
+constexpr int po_slots(int64_t m) { return m <= PO_NT ? 1 : m <= 2 * PO_NT ? 2 : m <= 4 * PO_NT ? 4 : 8; }
 // scratch of one panel: its values in the compute type, column-major (row
-// stride 1), then each row's position, then the pivots' rows
+// stride 1, `rows` a column: those of all threads), then each row's position,
+// then the pivots' rows
 template <typename CT> struct PoScratch {
     CT *v;
+    int rows;
     int *pos, *prow;
-    __host__ __device__ explicit PoScratch(void *base)
-        : v((CT *)base), pos((int *)(v + (size_t)NB_LEAF * PO_MAX_ROWS)), prow(pos + PO_MAX_ROWS)
+    __device__ __forceinline__ PoScratch(void *base, int slots)
+        : v((CT *)base), rows(PO_NT * slots), pos((int *)(v + (size_t)NB_LEAF * rows)), prow(pos + rows)
     {
     }
-    static constexpr size_t bytes = (size_t)NB_LEAF * PO_MAX_ROWS * sizeof(CT) + (PO_MAX_ROWS + NB_LEAF) * 4;
-    __device__ __forceinline__ CT &at(int k, int row) const { return v[k * PO_MAX_ROWS + row]; }
+    static size_t bytes(int slots)
+    {
+        return (size_t)PO_NT * slots * (NB_LEAF * sizeof(CT) + 4) + NB_LEAF * 4;
+    }
+    __device__ __forceinline__ CT &at(int k, int row) const { return v[k * rows + row]; }
 };
 
 // f(0), f(1), ... f(N - 1), each with its index as a compile-time constant
@@ -800,7 +807,7 @@ __global__ __launch_bounds__(PO_NT) void k_pivot_one(int64_t Np, int64_t c0, con
     __shared__ int pivs[L], prow[L];  // column k: the pivot's position, and its row
     __shared__ int moves;
     if (threadIdx.x == 0) moves = 0;
-    const PoScratch<CT> sc(scratch);
+    const PoScratch<CT> sc(scratch, R);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = (int)(Np - c0);
     if (block_flag(&flags[FLAG_TIMEOUT])) {
@@ -1186,7 +1193,7 @@ template <typename T, bool ONE>
 __global__ __launch_bounds__(256) void k_gather_u12(T *__restrict__ A, int64_t lda,
                                                     const int *__restrict__ list, int64_t c0,
                                                     int64_t k0, int64_t kend, T *__restrict__ LT,
-                                                    void *__restrict__ scratch,
+                                                    void *__restrict__ scratch, int slots,
                                                     int *__restrict__ flags)
 {
     typedef typename compute_of<T>::type CT;
@@ -1196,7 +1203,7 @@ __global__ __launch_bounds__(256) void k_gather_u12(T *__restrict__ A, int64_t l
         const int ncb = (int)((kend - k0 - L + 3) / 4);
         if ((int)blockIdx.x >= ncb) {
             __shared__ T buf[L][L + 2];
-            store_panel<T, CT>(PoScratch<CT>(scratch), (int)blockIdx.x - ncb, A, lda, LT, c0, k0, buf, flags);
+            store_panel<T, CT>(PoScratch<CT>(scratch, slots), (int)blockIdx.x - ncb, A, lda, LT, c0, k0, buf, flags);
             return;
         }
     }
@@ -1222,7 +1229,7 @@ __global__ __launch_bounds__(256) void k_gather_u12(T *__restrict__ A, int64_t l
         }
     }
     if constexpr (ONE) {
-        const PoScratch<CT> sc(scratch);
+        const PoScratch<CT> sc(scratch, slots);
         for (int i = t; i < L * L; i += 256) {
             const int r = i % L, j = i / L;
             Lm[r][j] = (CT)to_f32(to_store_d<T>((double)sc.at(j, sc.prow[r])));  // as stored
@@ -1299,20 +1306,17 @@ static int64_t pc_words(int prec, int64_t Np)
            pmax * nwv * NB_LEAF * W;
 }
 
-static size_t pc_exchange_bytes(int prec, int64_t Np)
+// exchange words and lists
+size_t pivot_xch_bytes(int prec, int64_t Np)
 {
     return (size_t)pc_words(prec, Np) * 8 + ((size_t)PC_NLIST * PC_LIST_INTS + PC_COMP_INTS) * 4;
 }
 
-// exchange words and lists, then the one-workgroup panel's scratch
-size_t pivot_xch_bytes(int prec, int64_t Np)
+// of the largest panel that one workgroup takes
+size_t pivot_panel_bytes(int prec, int64_t Np)
 {
-    return (size_t)round_up((int64_t)pc_exchange_bytes(prec, Np), 256) +
-           (prec == N3P_FP64 ? PoScratch<double>::bytes : PoScratch<float>::bytes);
-}
-static void *po_scratch(int prec, int64_t Np, void *xch)
-{
-    return (char *)xch + round_up((int64_t)pc_exchange_bytes(prec, Np), 256);
+    const int slots = po_slots(std::min<int64_t>(Np, PO_MAX_ROWS));
+    return prec == N3P_FP64 ? PoScratch<double>::bytes(slots) : PoScratch<float>::bytes(slots);
 }
 
 static const int *pc_lists(int prec, int64_t Np, const void *xch)
@@ -1322,7 +1326,7 @@ static const int *pc_lists(int prec, int64_t Np, const void *xch)
 
 hipError_t launch_pivot_reset(int prec, int64_t Np, void *xch, hipStream_t s)
 {
-    return launch_fill_i32((int *)xch, 0, (int64_t)(pc_exchange_bytes(prec, Np) / 4), s);
+    return launch_fill_i32((int *)xch, 0, (int64_t)(pivot_xch_bytes(prec, Np) / 4), s);
 }
 
 template <typename T, typename CT>
@@ -1335,39 +1339,40 @@ static hipError_t pivot_coop_t(int64_t Np, int64_t c0, int64_t k0, void *A, int6
     return hipGetLastError();
 }
 
-// R rows per thread for m rows, as few as hold them; at eight FP64 rows the
-// sub-panels are half as wide, so that SW R values fit the registers
+// As few rows per thread as hold the panel; at eight FP64 rows the sub-panels
+// are half as wide, so that SW R values fit the registers
 template <typename T, typename CT>
 static hipError_t pivot_one_t(int64_t Np, int64_t c0, const void *A, int64_t lda, int32_t *ipiv,
                               void *scratch, int *list, int *flags, hipStream_t s)
 {
-    const int64_t m = Np - c0;
     constexpr int SW8 = sizeof(CT) == 8 ? 8 : 16;
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(1), dim3(PO_NT), 0, s, Np, c0, (const T *)A, lda, ipiv,
                            scratch, list, flags);
     };
-    if (m <= PO_NT) go(k_pivot_one<T, CT, 16, 1>);
-    else if (m <= 2 * PO_NT) go(k_pivot_one<T, CT, 16, 2>);
-    else if (m <= 4 * PO_NT) go(k_pivot_one<T, CT, 16, 4>);
-    else go(k_pivot_one<T, CT, SW8, 8>);
+    switch (po_slots(Np - c0)) {
+    case 1: go(k_pivot_one<T, CT, 16, 1>); break;
+    case 2: go(k_pivot_one<T, CT, 16, 2>); break;
+    case 4: go(k_pivot_one<T, CT, 16, 4>); break;
+    default: go(k_pivot_one<T, CT, SW8, 8>);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void *A, int64_t lda,
-                             int32_t *ipiv, void *LT, void *xch, int *flags, hipStream_t s)
+                             int32_t *ipiv, void *LT, void *xch, void *panel, int *flags,
+                             hipStream_t s)
 {
     const int64_t rw = pc_rows_per_wg(prec), m = Np - c0;
     const int64_t P = (m + rw - 1) / rw, pmax = pc_pmax(prec, Np);
     if (m < NB_LEAF || m % NB_LEAF || P > PIVOT_MAX_WG) return hipErrorInvalidValue;
     int *list = const_cast<int *>(pc_lists(prec, Np, xch)) + ((c0 - k0) / NB_LEAF) * PC_LIST_INTS;
     if (m <= PO_MAX_ROWS) {
-        void *sc = po_scratch(prec, Np, xch);
         switch (prec) {
-        case N3P_FP16: return pivot_one_t<f16, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
-        case N3P_BF16: return pivot_one_t<bf16, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
-        case N3P_FP32: return pivot_one_t<float, float>(Np, c0, A, lda, ipiv, sc, list, flags, s);
-        case N3P_FP64: return pivot_one_t<double, double>(Np, c0, A, lda, ipiv, sc, list, flags, s);
+        case N3P_FP16: return pivot_one_t<f16, float>(Np, c0, A, lda, ipiv, panel, list, flags, s);
+        case N3P_BF16: return pivot_one_t<bf16, float>(Np, c0, A, lda, ipiv, panel, list, flags, s);
+        case N3P_FP32: return pivot_one_t<float, float>(Np, c0, A, lda, ipiv, panel, list, flags, s);
+        case N3P_FP64: return pivot_one_t<double, double>(Np, c0, A, lda, ipiv, panel, list, flags, s);
         }
         return hipErrorInvalidValue;
     }
@@ -1383,7 +1388,8 @@ hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void 
 // after launch_pivot_coop of the same leaf: also stores the panel it left in
 // its scratch (panels of at most PO_MAX_ROWS rows)
 hipError_t launch_gather_u12(int prec, int64_t Np, int64_t c0, int64_t k0, int64_t kend, void *A,
-                             int64_t lda, void *LT, void *xch, int *flags, hipStream_t s)
+                             int64_t lda, void *LT, void *xch, void *panel, int *flags,
+                             hipStream_t s)
 {
     const int64_t ncol = kend - k0 - NB_LEAF, m = Np - c0;
     const bool one = m <= PO_MAX_ROWS;
@@ -1391,13 +1397,13 @@ hipError_t launch_gather_u12(int prec, int64_t Np, int64_t c0, int64_t k0, int64
     if (grid == 0) return hipSuccess;
     if (m % 64) return hipErrorInvalidValue;
     const int *list = pc_lists(prec, Np, xch) + ((c0 - k0) / NB_LEAF) * PC_LIST_INTS;
-    void *sc = po_scratch(prec, Np, xch);
+    const int slots = one ? po_slots(m) : 0;
     const auto go = [&](auto t) {
         typedef decltype(t) T;
         if (one)
-            hipLaunchKernelGGL((k_gather_u12<T, true>), dim3(grid), dim3(256), 0, s, (T *)A, lda, list, c0, k0, kend, (T *)LT, sc, flags);
+            hipLaunchKernelGGL((k_gather_u12<T, true>), dim3(grid), dim3(256), 0, s, (T *)A, lda, list, c0, k0, kend, (T *)LT, panel, slots, flags);
         else
-            hipLaunchKernelGGL((k_gather_u12<T, false>), dim3(grid), dim3(256), 0, s, (T *)A, lda, list, c0, k0, kend, (T *)LT, sc, flags);
+            hipLaunchKernelGGL((k_gather_u12<T, false>), dim3(grid), dim3(256), 0, s, (T *)A, lda, list, c0, k0, kend, (T *)LT, panel, slots, flags);
         return hipGetLastError();
     };
     switch (prec) {

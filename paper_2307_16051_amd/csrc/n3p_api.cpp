@@ -82,6 +82,7 @@ struct FactorWs {
     void *LT = nullptr;       // Np x NB_OUT
     void *DG = nullptr;       // 2 x NB_LEAF^2
     void *xch = nullptr;      // pivoting path: exchange words and interchange list
+    void *panel = nullptr;    // pivoting path: a one-workgroup leaf's panel
     int32_t *ipiv = nullptr;  // Np
     int32_t *perm = nullptr;  // Np (device), valid if pivoted
     DevState *state = nullptr;  // flags, and the norms read back with them
@@ -107,7 +108,13 @@ size_t factor_bytes(int prec, int64_t n, Bump &b, FactorWs *f, char *base)
     size_t oF = b.take(sizeof(DevState));
     size_t oPub = top_path(prec) ? b.take(top_pub_words() * 8) : 0;
     size_t oInv = top_path(prec) ? b.take(top_inv_floats() * 4) : 0;
+    // the publication words are idle on the pivoting path and cleared by the
+    // next attempt without interchanges: the panel lies over them
+    const size_t panel = pivot_panel_bytes(prec, Np);
+    const bool over = top_path(prec) && panel <= top_pub_words() * 8;
+    size_t oPanel = over ? oPub : b.take(panel);
     if (f && base) {
+        f->panel = base + oPanel;
         f->pub = top_path(prec) ? (uint64_t *)(base + oPub) : nullptr;
         f->inv = top_path(prec) ? (float *)(base + oInv) : nullptr;
         f->prec = prec;
@@ -299,8 +306,9 @@ int getrf_pivot(const FactorWs &f, hipStream_t s)
         char *LT = LTb[blk & 1];
         auto lt = [&](int64_t row, int64_t col) { return (const void *)(LT + ((size_t)row * NB_OUT + (size_t)col) * es); };
         for (int64_t c0 = k0; c0 < kend; c0 += NB_LEAF) {
-            HIPCHK(launch_pivot_coop(prec, Np, c0, k0, f.A, lda, f.ipiv, LT, f.xch, f.flags, s));
-            HIPCHK(launch_gather_u12(prec, Np, c0, k0, kend, f.A, lda, LT, f.xch, f.flags, s));
+            HIPCHK(launch_pivot_coop(prec, Np, c0, k0, f.A, lda, f.ipiv, LT, f.xch, f.panel, f.flags,
+                                     s));
+            HIPCHK(launch_gather_u12(prec, Np, c0, k0, kend, f.A, lda, LT, f.xch, f.panel, f.flags, s));
             const int64_t c1 = c0 + NB_LEAF;
             if (c1 < kend) {
                 HIPCHK(launch_gemm_sub(prec, Np - c1, kend - c1, NB_LEAF, lt(c1, c0 - k0), NB_OUT,

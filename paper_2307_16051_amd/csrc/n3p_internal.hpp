@@ -233,14 +233,19 @@ hipError_t launch_top_gemm(int prec, int64_t k0, int W, void *A, int64_t lda, vo
                            const void *At2, const void *B2, void *C2, hipStream_t s);
 hipError_t launch_trsm(int prec, int64_t Np, int64_t k0, int W, void *A, int64_t lda, void *LT,
                        const float *inv, int *flags, hipStream_t s);
-// pivoting path: exchange area size (bytes), its reset, the cooperative leaf
+// pivoting path: exchange area size (bytes), the size of the panel area where
+// a leaf of one workgroup leaves its panel for launch_gather_u12 (contents are
+// of no use to anyone else or later), the exchange area's reset, the leaf
 // panel, the row moves of its interchanges, the LT rebuild of an outer block
 size_t pivot_xch_bytes(int prec, int64_t Np);
+size_t pivot_panel_bytes(int prec, int64_t Np);
 hipError_t launch_pivot_reset(int prec, int64_t Np, void *xch, hipStream_t s);
 hipError_t launch_pivot_coop(int prec, int64_t Np, int64_t c0, int64_t k0, void *A, int64_t lda,
-                             int32_t *ipiv, void *LT, void *xch, int *flags, hipStream_t s);
+                             int32_t *ipiv, void *LT, void *xch, void *panel, int *flags,
+                             hipStream_t s);
 hipError_t launch_gather_u12(int prec, int64_t Np, int64_t c0, int64_t k0, int64_t kend, void *A,
-                             int64_t lda, void *LT, void *xch, int *flags, hipStream_t s);
+                             int64_t lda, void *LT, void *xch, void *panel, int *flags,
+                             hipStream_t s);
 hipError_t launch_gather_block(int prec, int64_t Np, int64_t k0, int64_t kend, void *A,
                                int64_t lda, const void *xch, hipStream_t s);
 hipError_t launch_lt_rebuild(int prec, int64_t Np, int64_t r0, int64_t k0, int64_t ncol,

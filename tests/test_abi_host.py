@@ -166,3 +166,25 @@ def test_traffic_counters_are_keyed_to_kernels_and_schedule(tmp_path):
     (dst / "n3p_api.cpp").write_text(api)
     (dst / "k_getrf.hip").write_text((dst / "k_getrf.hip").read_text() + "\n")
     assert bench.factor_source_sha(str(root2)) != base
+
+
+# bytes of the matrix copy, L transposed, the exchange area, vectors and (half
+# precision) the diagonal square's areas, as (n, prec): a workspace holds these
+# and, in FP32 and FP64, one panel of the pivoting path
+GETRF_PARTS = {
+    (1, 0): 12145152, (64, 1): 12145152, (256, 2): 3240192, (64, 3): 6433536,
+    (600, 0): 15841280, (600, 2): 8509184, (1024, 3): 16958720, (2048, 0): 26379264,
+    (2048, 2): 25338624, (4096, 1): 60038144, (4096, 3): 168190208, (16384, 2): 1141754624,
+}
+
+
+@pytest.mark.parametrize("n,prec", sorted(GETRF_PARTS))
+def test_getrf_workspace_holds_a_panel_of_the_matrix_only(lib, n, prec):
+    """The panel that one workgroup factors has as many rows as the matrix,
+    rounded up to the workgroup's (512, 1024, 2048 or 4096), not 4096 at every
+    size; the half precisions put it over areas that are idle at that time."""
+    f = lib.n3p_getrf_workspace_size
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int64, ctypes.c_int]
+    rows = next((r for r in (512, 1024, 2048) if (n + 255) // 256 * 256 <= r), 4096)
+    panel = 0 if prec < 2 else rows * (64 * (4 if prec == 2 else 8) + 4) + 64 * 4
+    assert f(n, prec) <= GETRF_PARTS[n, prec] + (panel + 511) // 256 * 256
