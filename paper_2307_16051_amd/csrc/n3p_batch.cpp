@@ -69,7 +69,7 @@ size_t request_layout(int64_t n, int prec, BDesc *d, char *base)
                  oCS = take((size_t)Np * 4), ox = take((size_t)n * 8), oF = take((size_t)n * 8),
                  oD = take((size_t)n * 8), oh = take((size_t)2 * n * 8), ob = take((size_t)Np * 4),
                  ou = take((size_t)Np * 4), oup = take((size_t)Np * 4), orr = take((size_t)Np * 4),
-                 oy = take((size_t)Np * 4), ofl = take((size_t)NFLAGS * 4);
+                 ofl = take((size_t)NFLAGS * 4);
     if (d && base) {
         std::memset(d, 0, sizeof(*d));
         d->n = n;
@@ -88,7 +88,6 @@ size_t request_layout(int64_t n, int prec, BDesc *d, char *base)
         d->u = (float *)(base + ou);
         d->uprev = (float *)(base + oup);
         d->r = (float *)(base + orr);
-        d->y = (float *)(base + oy);
         d->flags = (int *)(base + ofl);
     }
     return off;

@@ -366,14 +366,18 @@ struct BDesc {
     int prec;            // N3P_FP16 or N3P_BF16
     int pad_;
     void *A;             // factor buffer, Np x Np column-major (ld Np), identity padding
-    void *LT;            // L of the current leaf, transposed: row i at LT + 64 i
+    // L of the current leaf, transposed: row i at LT + 64 i.  Idle once the
+    // matrix is factored: the solves by blocks keep their words (Np of 8 bytes)
+    // and y (Np of 4) in it
+    void *LT;
     void *DG;            // 2 x 64 x 64 factored diagonal blocks
     float *J;            // n x n FP32 Jacobian, ld n
     float *colscale;     // Np
     double *x, *F, *D, *h;          // n, n, n, 2n
-    float *b, *u, *uprev, *r, *y;   // Np each
+    float *b, *u, *uprev, *r;       // Np each
     int *flags;          // NFLAGS
 };
+static_assert(B_LEAF * 2 >= 8 + 4, "a row of LT (half precision) holds a word and an entry of y");
 
 struct BState {
     int phase, status, its, factor;

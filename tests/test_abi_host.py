@@ -188,3 +188,17 @@ def test_getrf_workspace_holds_a_panel_of_the_matrix_only(lib, n, prec):
     rows = next((r for r in (512, 1024, 2048) if (n + 255) // 256 * 256 <= r), 4096)
     panel = 0 if prec < 2 else rows * (64 * (4 if prec == 2 else 8) + 4) + 64 * 4
     assert f(n, prec) <= GETRF_PARTS[n, prec] + (panel + 511) // 256 * 256
+
+
+@pytest.mark.parametrize("slots,fixed", [(1, 1536), (8, 8448), (64, 63744), (256, 254208)])
+@pytest.mark.parametrize("n,request_bytes", [(1, 35840), (64, 53504), (100, 113920), (512, 1687808),
+                                             (2048, 25575680), (4096, 101466368)])
+def test_engine_pool_holds_what_it_held(lib, slots, fixed, n, request_bytes):
+    """A pool for `slots` slots and one request of n rows, as sized when a
+    request's solves had one workgroup and a vector of their own: the tickets
+    of the solves by blocks have to fit into it too."""
+    f, r = lib.n3p_engine_fixed_bytes, lib.n3p_engine_request_bytes
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int]
+    r.restype, r.argtypes = ctypes.c_size_t, [ctypes.c_int64, ctypes.c_int]
+    for prec in (0, 1):
+        assert f(slots) + r(n, prec) <= fixed + request_bytes
