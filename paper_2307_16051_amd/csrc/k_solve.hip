@@ -22,21 +22,6 @@ namespace n3p {
 
 constexpr int SPIN_LIMIT = 1 << 24;
 
-__device__ __forceinline__ bool wait_epoch(int *f, uint32_t epoch, int *flags)
-{
-    int spins = 0;
-    while ((uint32_t)__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
-        __builtin_amdgcn_s_sleep(2);
-        if (++spins > SPIN_LIMIT) {
-            set_flag(&flags[FLAG_TIMEOUT], 1);
-            return false;
-        }
-    }
-    return true;
-}
-
-template <typename V> __device__ __forceinline__ V shfl_v(V v, int src) { return __shfl(v, src); }
-
 // Solution values are published as 64-bit words (epoch << 32 | 32 bits of
 // data): FP32 values take one word, FP64 values two.  A reader polls the words
 // it needs until their tag equals the launch's epoch, so the value arrives in
@@ -51,17 +36,6 @@ template <> struct tagged<float> {
         const uint64_t w = ((uint64_t)ep << 32) | (uint32_t)__float_as_uint(v);
         __hip_atomic_store(&t[i], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    static __device__ __forceinline__ float get(const uint64_t *t, int64_t i, uint32_t ep, int *spins,
-                                                int *flags)
-    {
-        uint64_t w = __hip_atomic_load(&t[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while ((uint32_t)(w >> 32) != ep) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++*spins > SPIN_LIMIT) { set_flag(&flags[FLAG_TIMEOUT], 1); break; }
-            w = __hip_atomic_load(&t[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        return __uint_as_float((uint32_t)w);
-    }
 };
 template <> struct tagged<double> {
     static constexpr int W = 2;
@@ -72,21 +46,6 @@ template <> struct tagged<double> {
                            __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&t[2 * i + 1], ((uint64_t)ep << 32) | (b >> 32), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-    }
-    static __device__ __forceinline__ double get(const uint64_t *t, int64_t i, uint32_t ep, int *spins,
-                                                 int *flags)
-    {
-        uint32_t part[2];
-        for (int h = 0; h < 2; ++h) {
-            uint64_t w = __hip_atomic_load(&t[2 * i + h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while ((uint32_t)(w >> 32) != ep) {
-                __builtin_amdgcn_s_sleep(1);
-                if (++*spins > SPIN_LIMIT) { set_flag(&flags[FLAG_TIMEOUT], 1); break; }
-                w = __hip_atomic_load(&t[2 * i + h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            part[h] = (uint32_t)w;
-        }
-        return __longlong_as_double((long long)(((uint64_t)part[1] << 32) | part[0]));
     }
 };
 
@@ -330,20 +289,10 @@ __device__ __forceinline__ void diag_inverse_mx(V *__restrict__ Dr, const V *__r
     }
 }
 
-// sum_c r[c] v[c] with v held one value per lane, four independent partial sums.
-template <typename V, int BS>
-__device__ __forceinline__ V row_times_lanes(const V (&r)[BS], V v)
-{
-    V a[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int c = 0; c < BS; ++c) a[c & 3] += r[c] * lane_bcast(v, c);
-    return (a[0] + a[1]) + (a[2] + a[3]);
-}
-// The same product with v passed through LDS (vb: this wavefront's BS
-// entries): one store and BS/4 broadcast reads instead of BS readlanes,
-// which the compiler chains through one SGPR with a wait state each.
-// (Same sums in the same order as row_times_lanes, so the same result.)
-// vb must be 16-byte aligned.
+// sum_c r[c] v[c] with v held one value per lane and passed through LDS (vb:
+// this wavefront's BS entries), four independent partial sums: one store and
+// BS/4 broadcast reads instead of BS readlanes, which the compiler chains
+// through one SGPR with a wait state each.  vb must be 16-byte aligned.
 template <typename V, int BS>
 __device__ __forceinline__ V row_times_lds(const V (&r)[BS], V v, V *vb, int lane)
 {
