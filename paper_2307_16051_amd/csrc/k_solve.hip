@@ -950,6 +950,11 @@ hipError_t launch_krylov_update(int64_t n, const float *V, int64_t ldv, int k, c
 // and y lie in the slot's LT, which only the factorisation uses; k_b_ir_init
 // clears the words each Newton step and the tags count the sweeps, so no tag
 // repeats.  The tickets are cleared by the sweep's k_b_ir_check.
+// These blocks multiply by explicit FP32 inverses of the diagonal blocks where
+// the first form substitutes.  One solve with FP16 or BF16 factors of the
+// H-equation's Jacobian at the solution, N = 512 to 4096 and c = 0.9 to 0.999999,
+// is 0.8 to 1.3e-7 from 64 bits this way and 4e-7 to 1.6e-6 by row-by-row
+// substitution: the shorter sums gain more than the inverses cost.
 // With one workgroup per slot the 32 blocks of N = 2048 passed through one
 // CU: 347 us a call for 32 requests of 128 to 2048 rows, now 101 for the two
 // launches (240 for one workgroup with the substitution of a block beside the

@@ -253,3 +253,61 @@ def test_engine_small_requests_alone_and_beside_large_ones(env, prec):
                 assert torch.equal(x, xs[n]), (n, c)
             xs[n] = x
         eng.close()
+
+
+@pytest.mark.parametrize("prec", ["FP16", "BF16"])
+def test_engine_ill_conditioned_requests(env, prec):
+    """c near one: the Jacobian nears singularity at the solution, refinement
+    needs more sweeps, and the solves by blocks (explicit inverses of the
+    diagonal blocks) have to carry it as substitution does."""
+    n3p, torch = env
+    reqs = [(200, 0.9999), (300, 0.9999), (512, 0.9999), (1024, 0.9999), (300, 0.99999), (1024, 0.99999)]
+    print("case engine ill-conditioned %s" % prec, flush=True)
+    p = getattr(n3p, prec)
+    cfg = n3p.EngineConfig.default(max_slots=8, lu_prec=p)
+    eng = n3p.Engine(make_pool(n3p, torch, [n for n, _ in reqs], 8, p), cfg)
+    slots = [eng.admit(n, c) for n, c in reqs]
+    run_to_completion(eng, slots)
+    for (n, c), s in zip(reqs, slots):
+        x = torch.empty(n, dtype=torch.float64, device="cuda")
+        rep = eng.collect(s, x)
+        ref = O.newton_heq(n, c)
+        err = rel_err(x.cpu().numpy(), ref.x_floor)
+        print("  n=%d c=%g its=%d (oracle %d) err=%.2e" % (n, c, rep.its, ref.its, err), flush=True)
+        assert rep.status == 0 and rep.its in (ref.its, ref.its + 1), (n, c)
+        assert err <= 1e-9, (n, c)
+    eng.close()
+
+
+@pytest.mark.parametrize("prec", ["FP16", "BF16"])
+@pytest.mark.parametrize("n,c", [(320, 0.9), (512, 0.9999), (1024, 0.99999)])
+def test_solve_by_blocks_is_as_accurate_as_substitution(env, prec, n, c):
+    """One solve with half-precision factors of the Jacobian at the solution,
+    by the row blocks that the engine and the single solves share, against 64
+    bits with the same factors: no further off than row-by-row substitution
+    in FP32."""
+    n3p, torch = env
+    J = torch.from_numpy(O.heq_jacobian(O.newton_heq(n, c).x_floor, c)).cuda()
+    J = J * 2.0 ** torch.floor(9 - torch.log2(J.abs().amax(0)))[None, :]
+    LU = J.t().contiguous().to({"FP16": torch.float16, "BF16": torch.bfloat16}[prec]).t()
+    ipiv, info = n3p.getrf(LU)
+    assert info == 0
+    perm = torch.from_numpy(O.perm_from_ipiv(ipiv.cpu().numpy())).cuda()
+    L64, A = LU.double(), LU.float()
+    errs = {"blocks": [], "substitution": []}
+    for seed in range(4):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        b = torch.randn(n, generator=g, device="cuda", dtype=torch.float32)
+        ref = torch.linalg.solve_triangular(L64, b.double()[perm][:, None], upper=False, unitriangular=True)
+        ref = torch.linalg.solve_triangular(L64, ref, upper=True)[:, 0]
+        y = b[perm]
+        for k in range(n - 1):
+            y[k + 1:] = torch.addcmul(y[k + 1:], A[k + 1:, k], y[k], value=-1)
+        for k in range(n - 1, -1, -1):
+            y[k] = y[k] * (1.0 / A[k, k])
+            y[:k] = torch.addcmul(y[:k], A[:k, k], y[k], value=-1)
+        for name, x in (("blocks", n3p.getrs(LU, ipiv, b.clone())), ("substitution", y)):
+            errs[name].append(float((x.double() - ref).norm() / ref.norm()))
+    print("  %s n=%d c=%g error: blocks %.2e substitution %.2e" % (
+        prec, n, c, np.mean(errs["blocks"]), np.mean(errs["substitution"])), flush=True)
+    assert np.mean(errs["blocks"]) <= np.mean(errs["substitution"])
