@@ -60,7 +60,7 @@ __device__ __forceinline__ double recip(double v) { return 1.0 / v; }
 // coefficients, 64 per lane and group of 8 steps, kept the LDS busy).  The
 // panel loop is unrolled for constant lanes in the broadcasts (FP64: 20 -> 17
 // us).  Measured: k_leaf_spec<double> 29.2 -> 17.1 us (2 and 92 tiles alike);
-// the batched FP16 leaf 25 -> 17 us, 35 -> 32 us with four tiles a CU.
+// the batched FP16 leaf 25.2 -> 18.4 us, 35 -> 32 us with four tiles a CU.
 constexpr int LEAF_THREADS = 512;
 
 // eight consecutive elements (16-byte aligned) to and from the compute type

@@ -1049,8 +1049,9 @@ __device__ __forceinline__ int stage_split(TrsmCtx<T> &c, const float (&y)[16], 
 #pragma unroll
     for (int q = 0; q < 16; ++q) mx = fmaxf(mx, fabsf(y[q]));
     // the four maxima cross through the head of each wavefront's own part of
-    // pbuf, which it has read and which is written again only after the next
-    // block's first barrier
+    // pbuf, which it has read (join_halves); they are read before the barrier
+    // that follows this function, and waves 4..7 write pbuf again in the next
+    // block's join_halves, which they enter after this block's last barrier
     mx = wave_max(mx);
     if (c.w < 4 && (threadIdx.x & 63) == 0) c.pbuf[c.w * 1024] = mx;
     __syncthreads();

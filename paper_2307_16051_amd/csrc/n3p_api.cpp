@@ -203,11 +203,11 @@ int getrf_spec(const FactorWs &f, hipStream_t s)
 // partial-pivoting rule), one outer block of up to NB_OUT columns at a time,
 // with look-ahead: block j's L below its square and U right of it (k_trsm),
 // the update of block j + 1's square, then that square factored in the same
-// launch as the rest of block j's update (the rows below the square included).  LT alternates between
-// two buffers by block parity.  Publication tags are unique within a
-// factorisation (launch_init_state clears the area).
+// launch as the rest of block j's update (the rows below the square included).
+// LT alternates between two buffers by block parity.  Publication tags are
+// unique within a factorisation (launch_init_state clears the area).
 // The last square ends with the last leaf that holds a column of the matrix
-// (20 us a leaf: n = 256 took eight leaves for four).  Up to two squares there
+// (17 us a leaf: n = 256 would take eight leaves for four).  Up to two squares there
 // is no 256 x 256 update, so everything else ends there too; beyond, the
 // updates cover the padding (zeros), which keeps their tiles whole.
 int getrf_spec_top(const FactorWs &f, hipStream_t s)
