@@ -956,7 +956,7 @@ hipError_t launch_krylov_update(int64_t n, const float *V, int64_t ldv, int k, c
 // is 0.8 to 1.3e-7 from 64 bits this way and 4e-7 to 1.6e-6 by row-by-row
 // substitution: the shorter sums gain more than the inverses cost.
 // With one workgroup per slot the 32 blocks of N = 2048 passed through one
-// CU: 347 us a call for 32 requests of 128 to 2048 rows, now 101 for the two
+// CU: 347 us a call for 32 requests of 128 to 2048 rows, now 98 for the two
 // launches (240 for one workgroup with the substitution of a block beside the
 // update by the one before it).
 template <typename T>
